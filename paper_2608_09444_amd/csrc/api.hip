@@ -111,6 +111,14 @@ WsLayout ws_layout(const cdb_model_desc& d, int rows) {
     off = align256(off + 3 * M * 4);
     L.lm = off;  // prefill without logits: the LM head of the last 32-row tile
     off = align256(off + (size_t)32 * d.vocab * 4);
+    L.base = off;
+    // segment records and arrival counters of the split attention, for as many
+    // rows as it takes (also in larger workspaces, which serve smaller calls)
+    const size_t split = std::min(rows, (kAttnSplitItems - 1) / d.n_heads);
+    L.apart = off;
+    off = align256(off + split * attn_part_floats(d.n_heads, d.head_dim) * 4);
+    L.arrive = off;
+    off = align256(off + split * d.n_heads * 4);
     L.total = off;
     return L;
 }
@@ -136,10 +144,11 @@ struct Ctx {
     int32_t* deff;
     int32_t* prow;
     float* lm;
+    AttnScratch asplit;  // arrive: NULL for calls of too many rows to split
 };
 
 static Ctx make_ctx(const cdb_model* model, void* ws, int rows) {
-    Ctx c;
+    Ctx c{};
     c.md = &model->desc;
     c.wb = static_cast<const unsigned char*>(model->packed);
     weight_layout(model->desc, &c.wl);
@@ -159,6 +168,8 @@ static Ctx make_ctx(const cdb_model* model, void* ws, int rows) {
     c.deff = reinterpret_cast<int32_t*>(c.ws + c.L.deff);
     c.prow = reinterpret_cast<int32_t*>(c.ws + c.L.prow);
     c.lm = reinterpret_cast<float*>(c.ws + c.L.lm);
+    if (rows * model->desc.n_heads < kAttnSplitItems)
+        c.asplit = AttnScratch{reinterpret_cast<float*>(c.ws + c.L.apart), reinterpret_cast<int*>(c.ws + c.L.arrive)};
     return c;
 }
 
@@ -215,7 +226,8 @@ static cdb_status run_layers(const Ctx& c, int first, int count, KvTarget kv, co
             HIPCHK(launch_prefill_attention(c.q, kv, chunk->seq, chunk->pos0, M, d.n_heads, d.head_dim, c.x, c.err,
                                             st));
         else
-            HIPCHK(launch_attention(c.q, kv, r.seq, r.pos, c.order, M, d.n_heads, d.head_dim, c.x, c.err, st, dn));
+            HIPCHK(launch_attention(c.q, kv, r.seq, r.pos, c.order, M, d.n_heads, d.head_dim, c.x, c.err, st, dn,
+                                    c.asplit.arrive ? &c.asplit : nullptr));
         HIPCHK(launch_gemm(EPI_PARTIAL, c.x, wptr(c, lb + c.wl.o), M, c.gm.o, c.part, ea, st, dn));
         // MLP half: h += O partials; x = RMSNorm(h); act = SwiGLU; down partials
         HIPCHK(launch_resid_norm(c.h, c.part, c.gm.o.S, M, d.d, d.rms_eps, c.x, st, dn));
@@ -348,8 +360,7 @@ cdb_status cdb_boundary_prelude(const cdb_model* model, const cdb_kv* kv, const 
     Ctx c = make_ctx(model, ws, rows->n_rows);
     const KvTarget t = stage_target(d, *kv, 0);
     HIPCHK(launch_embed(d, wptr(c, c.wl.embed), tokens, *rows, *kv, t, state->n_slots, c.h, c.rope, c.kvpid, c.order,
-                        c.err,
-                        st));
+                        c.asplit.arrive, c.err, st));
     s = run_layers(c, 0, d.n_prelude, t, *rows, false, st);
     if (s != CDB_OK) return s;
     HIPCHK(launch_store_state(rows->n_rows, d.d, state->n_slots, rows->slot, c.h, state->h,
@@ -380,7 +391,7 @@ static cdb_status loop_step(const cdb_model* model, const cdb_kv* kv, const cdb_
         // the gather also writes the first core layer's input (the adapter's
         // input for injection models)
         HIPCHK(launch_gather(d, *state, r, *kv, t, c.h, c.h_in, d.injection ? c.x : nullptr, c.rope, c.kvpid, c.order,
-                             d.injection ? nullptr : c.x, c.err, st));
+                             c.asplit.arrive, d.injection ? nullptr : c.x, c.err, st));
         // injection models: the gather zeroed h; the adapter's split-K
         // partials become the first layer's input in its residual + norm
         if (d.injection) {
@@ -420,7 +431,11 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
 // process ends.  Host code never uses this name as an address (on the host it
 // is a stand-in symbol); it uses the device address hipGetSymbolAddress gives,
 // looked up once per device.
-constexpr size_t kNoAllocScratchBytes = (size_t)48 << 20;
+// Calls are accepted up to kNoAllocLimit bytes of the regions every call needs;
+// the split attention's come on top, at most 511 (row, head) pairs' records and
+// counters (17 MB).
+constexpr size_t kNoAllocLimit = (size_t)48 << 20;
+constexpr size_t kNoAllocScratchBytes = kNoAllocLimit + ((size_t)18 << 20);
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -449,7 +464,7 @@ cdb_status cdb_loop_step_noalloc(const cdb_model* model, const cdb_kv* kv, const
     if (!d_error || !model || !rows) return CDB_ERR_INVALID_ARG;
     if (!desc_supported(model->desc)) return CDB_ERR_UNSUPPORTED;
     if (rows->n_rows < 0) return CDB_ERR_INVALID_ARG;
-    if (rows->n_rows > kMaxRows || ws_layout(model->desc, rows->n_rows).total > kNoAllocScratchBytes)
+    if (rows->n_rows > kMaxRows || ws_layout(model->desc, rows->n_rows).base > kNoAllocLimit)
         return CDB_ERR_CAPACITY;
     void* ws = device_scratch();
     if (!ws) return CDB_ERR_HIP;
@@ -467,7 +482,7 @@ cdb_status cdb_boundary_coda(const cdb_model* model, const cdb_kv* kv, const cdb
     Ctx c = make_ctx(model, ws, M);
     const KvTarget t = stage_target(d, *kv, 2);
     HIPCHK(launch_load_state(d, M, rows->slot, rows->seq, rows->pos, t, state->h, state->n_slots, c.h, c.rope, c.kvpid,
-                             c.order, c.err, st, rows->d_n_rows));
+                             c.order, c.asplit.arrive, c.err, st, rows->d_n_rows));
     s = run_layers(c, d.n_prelude + d.n_core, d.n_coda, t, *rows, true, st);
     if (s != CDB_OK) return s;
     EpiArgs ea{};
@@ -503,7 +518,7 @@ cdb_status cdb_prefill(const cdb_model* model, const cdb_kv* kv, int32_t seq, in
     HIPCHK(launch_prefill_rows(seq, pos0, M, c.prow, st));
     // prelude (plane 0): embedding, RoPE table, write pages
     KvTarget t = stage_target(d, *kv, 0);
-    HIPCHK(launch_embed(d, wptr(c, c.wl.embed), tokens, r, *kv, t, M, c.h, c.rope, c.kvpid, nullptr, c.err, st));
+    HIPCHK(launch_embed(d, wptr(c, c.wl.embed), tokens, r, *kv, t, M, c.h, c.rope, c.kvpid, nullptr, nullptr, c.err, st));
     cdb_status s = run_layers(c, 0, d.n_prelude, t, r, false, st, &chunk);
     if (s != CDB_OK) return s;
     if (d.injection) HIPCHK(hipMemcpyAsync(c.h_in, c.h, (size_t)M * d.d * 4, hipMemcpyDeviceToDevice, st));  // e

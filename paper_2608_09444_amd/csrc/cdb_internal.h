@@ -112,7 +112,9 @@ struct WeightLayout {
 bool weight_layout(const cdb_model_desc& d, WeightLayout* out);
 
 struct WsLayout {
-    size_t err, h, h_in, q, x, act, part, rope, order, kvpid, deff, prow, lm, total;
+    size_t err, h, h_in, q, x, act, part, rope, order, kvpid, deff, prow, lm;
+    size_t base;  // bytes up to here; what follows speeds calls up but does not decide which calls are accepted
+    size_t apart, arrive, total;
 };
 WsLayout ws_layout(const cdb_model_desc& d, int rows);
 
@@ -124,11 +126,35 @@ bool desc_supported(const cdb_model_desc& d);
 // dn: optional device row count (<= M); rows at or past it are not stored
 hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, GemmShape g, float* part,
                        const EpiArgs& ea, hipStream_t st, const int32_t* dn = nullptr);
+// A row's context in the decode attention: segments of this many pages, a
+// function of the row's own page count (so that its result does not depend on
+// the call), at least 12 pages, a multiple of the 4 page classes and at most
+// kAttnMaxSegments segments.  Shorter segments give one row more workgroups (8
+// pages: 9.8 us against 10.8 with 12 and 11.5 with 16, 450 positions) but cost
+// more merging with several rows (9 Huginn-shaped rows 32, 28.5 and 28 us).
+constexpr int kAttnMaxSegments = 16;
+__host__ __device__ __forceinline__ int attn_segment_pages(int npg) {
+    const int p = (npg + 4 * kAttnMaxSegments - 1) / (4 * kAttnMaxSegments) * 4;
+    return p < 12 ? 12 : p;
+}
+// (row, head) pairs below which the decode attention spreads a row's segments
+// over several workgroups
+constexpr int kAttnSplitItems = 512;
+// Scratch of that form: segment records (attn_part_floats per row) and one
+// arrival counter per (row, head), zero between launches.
+struct AttnScratch {
+    float* part;
+    int* arrive;
+};
+__host__ __device__ __forceinline__ size_t attn_part_floats(int H, int hd) {
+    return (size_t)H * kAttnMaxSegments * 4 * (hd + 2);
+}
 // order: the call's rows ranked by descending position (by the row-entry
-// kernels of a stage call, or by launch_row_order)
+// kernels of a stage call, or by launch_row_order); scratch: NULL keeps every
+// row in one workgroup per head
 hipError_t launch_attention(const float* q, const KvTarget& kv, const int32_t* seq, const int32_t* pos,
                             const int32_t* order, int M, int H, int hd, uint16_t* out, int* err, hipStream_t st,
-                            const int32_t* dn = nullptr);
+                            const int32_t* dn = nullptr, const AttnScratch* scratch = nullptr);
 hipError_t launch_row_order(const int32_t* pos, int M, int32_t* order, hipStream_t st, const int32_t* dn = nullptr);
 // causal attention of a prefill chunk: rows are positions pos0..pos0+M-1 of one
 // sequence in the target's fixed plane
@@ -143,20 +169,21 @@ hipError_t launch_resid_norm(float* h, const float* part, int S, int M, int d, f
 // and kvpid[M], the page of the stage's pool that receives each row's K/V
 // (the page table looked up once per call; -1 and a device error if unmapped).
 // They (gather, embed, state load) also write the attention's row order when
-// `order` is non-null (at most kMaxRows rows).  The gather writes either the
-// adapter input xcat = [h; e] or, with xn set, the first core layer's input
+// `order` is non-null (at most kMaxRows rows), and clear the rows' arrival
+// counters of the split attention when `arrive` is.  The gather writes either
+// the adapter input xcat = [h; e] or, with xn set, the first core layer's input
 // xn = bf16(RMSNorm(h)), both in fragment layout.
 hipError_t launch_gather(const cdb_model_desc& md, const cdb_state& s, const cdb_rows& r, const cdb_kv& kv,
                          const KvTarget& kt, float* h, float* h_in, uint16_t* xcat, float2* rope, int32_t* kvpid,
-                         int32_t* order, uint16_t* xn, int* err, hipStream_t st);
+                         int32_t* order, int* arrive, uint16_t* xn, int* err, hipStream_t st);
 hipError_t launch_embed(const cdb_model_desc& md, const uint16_t* embed, const int32_t* tokens, const cdb_rows& r,
                         const cdb_kv& kv, const KvTarget& kt, int n_slots, float* h, float2* rope, int32_t* kvpid,
-                        int32_t* order, int* err, hipStream_t st);
+                        int32_t* order, int* arrive, int* err, hipStream_t st);
 hipError_t launch_store_state(int M, int d, int n_slots, const int32_t* slot, const float* h, float* state_h,
                               float* state_e, hipStream_t st, const int32_t* dn = nullptr);
 hipError_t launch_load_state(const cdb_model_desc& md, int M, const int32_t* slot, const int32_t* seq,
                              const int32_t* pos, const KvTarget& kt, const float* state_h, int n_slots, float* h,
-                             float2* rope, int32_t* kvpid, int32_t* order, int* err, hipStream_t st,
+                             float2* rope, int32_t* kvpid, int32_t* order, int* arrive, int* err, hipStream_t st,
                              const int32_t* dn = nullptr);
 // h += the S split-K partials in part (split order) first; gate: NULL replays
 // rows.depth; deff[M] receives each exiting row's depth.

@@ -50,6 +50,12 @@ __device__ __forceinline__ void row_order_block(const int32_t* __restrict__ pos,
     }
 }
 
+// Clears row i's arrival counters of the split attention (one per head).
+__device__ __forceinline__ void clear_arrivals(int* arrive, int i, int H) {
+    if (arrive)
+        for (int k = threadIdx.x; k < H; k += blockDim.x) arrive[(size_t)i * H + k] = 0;
+}
+
 // ------------------------------------------------------------------ gather
 // h[i] = state.h[slot[i]] (zeros with the adapter); h_in[i] = state.h[slot[i]]
 // (exit score of the L2 criterion); xcat[i] = bf16([h; e]) for the
@@ -82,14 +88,16 @@ __global__ __launch_bounds__(256) void k_gather(int d, int r_max, int n_slots, i
                                                 const float* __restrict__ sh, const float* __restrict__ se,
                                                 float* __restrict__ h, float* __restrict__ h_in,
                                                 uint16_t* __restrict__ xcat, float2* __restrict__ rope, KvTarget kt,
-                                                int32_t* __restrict__ kvpid, int32_t* __restrict__ order, float eps,
-                                                uint16_t* __restrict__ xn, int* err, const int32_t* __restrict__ dn) {
+                                                int32_t* __restrict__ kvpid, int32_t* __restrict__ order,
+                                                int* __restrict__ arrive, float eps, uint16_t* __restrict__ xn, int* err,
+                                                const int32_t* __restrict__ dn) {
     __shared__ float red[4];
     const int i = blockIdx.x;
     const int n = live_rows(dn, gridDim.x);
     if (order && i == 0 && gridDim.x <= kMaxRows) row_order_block(pos, n, order);
     if (i >= n) return;
     const int sl = slot[i];
+    clear_arrivals(arrive, i, d / hd);
     rope_row(pos[i], hd, base, rope + (size_t)i * (hd / 2));
     if (threadIdx.x == 0) {
         if (depth ? (depth[i] < 1 || depth[i] > r_max || c[i] < 0 || c[i] >= depth[i]) : (c[i] < 0 || c[i] >= r_max))
@@ -139,13 +147,14 @@ __global__ __launch_bounds__(256) void k_load_state(int d, int n_slots, int hd, 
                                                     const int32_t* __restrict__ pos, KvTarget kt,
                                                     const float* __restrict__ sh, float* __restrict__ h,
                                                     float2* __restrict__ rope, int32_t* __restrict__ kvpid,
-                                                    int32_t* __restrict__ order, int* err,
+                                                    int32_t* __restrict__ order, int* __restrict__ arrive, int* err,
                                                     const int32_t* __restrict__ dn) {
     const int i = blockIdx.x;
     const int n = live_rows(dn, gridDim.x);
     if (order && i == 0 && gridDim.x <= kMaxRows) row_order_block(pos, n, order);
     if (i >= n) return;
     const int sl = slot[i];
+    clear_arrivals(arrive, i, d / hd);
     rope_row(pos[i], hd, base, rope + (size_t)i * (hd / 2));
     const bool ok = sl >= 0 && sl < n_slots;
     if (threadIdx.x == 0) {
@@ -214,12 +223,13 @@ __global__ __launch_bounds__(256) void k_embed(int d, int vocab, int n_slots, in
                                                const int32_t* __restrict__ tok, const int32_t* __restrict__ slot,
                                                const int32_t* __restrict__ seq, const int32_t* __restrict__ pos,
                                                float* __restrict__ h, float2* __restrict__ rope, KvTarget kt,
-                                               int32_t* __restrict__ kvpid, int32_t* __restrict__ order, int* err,
-                                               const int32_t* __restrict__ dn) {
+                                               int32_t* __restrict__ kvpid, int32_t* __restrict__ order,
+                                               int* __restrict__ arrive, int* err, const int32_t* __restrict__ dn) {
     const int i = blockIdx.x;
     const int n = live_rows(dn, gridDim.x);
     if (order && i == 0 && gridDim.x <= kMaxRows) row_order_block(pos, n, order);
     if (i >= n) return;
+    clear_arrivals(arrive, i, d / hd);
     rope_row(pos[i], hd, base, rope + (size_t)i * (hd / 2));
     const int t = tok[i];
     const bool ok = t >= 0 && t < vocab;
@@ -569,24 +579,24 @@ static int page_cap(const cdb_kv& kv) { return kv.max_pages * kPage; }
 
 hipError_t launch_gather(const cdb_model_desc& md, const cdb_state& s, const cdb_rows& r, const cdb_kv& kv,
                          const KvTarget& kt, float* h, float* h_in, uint16_t* xcat, float2* rope, int32_t* kvpid,
-                         int32_t* order, uint16_t* xn, int* err, hipStream_t st) {
+                         int32_t* order, int* arrive, uint16_t* xn, int* err, hipStream_t st) {
     if (r.n_rows <= 0) return hipSuccess;
     if (order && r.n_rows > kMaxRows) return hipErrorInvalidValue;
     if (xcat && xn) return hipErrorInvalidValue;
     k_gather<<<r.n_rows, 256, 0, st>>>(md.d, md.r_max, s.n_slots, kv.max_seqs, page_cap(kv), md.head_dim, md.rope_base,
                                         r.slot, r.seq, r.pos, r.c, r.depth, s.h, s.e, h, h_in, xcat, rope, kt, kvpid,
-                                        order, md.rms_eps, xn, err, r.d_n_rows);
+                                        order, arrive, md.rms_eps, xn, err, r.d_n_rows);
     return hipGetLastError();
 }
 
 hipError_t launch_load_state(const cdb_model_desc& md, int M, const int32_t* slot, const int32_t* seq,
                              const int32_t* pos, const KvTarget& kt, const float* state_h, int n_slots, float* h,
-                             float2* rope, int32_t* kvpid, int32_t* order, int* err, hipStream_t st,
+                             float2* rope, int32_t* kvpid, int32_t* order, int* arrive, int* err, hipStream_t st,
                              const int32_t* dn) {
     if (M <= 0) return hipSuccess;
     if (order && M > kMaxRows) return hipErrorInvalidValue;
     k_load_state<<<M, 256, 0, st>>>(md.d, n_slots, md.head_dim, md.rope_base, slot, seq, pos, kt, state_h, h, rope,
-                                    kvpid, order, err, dn);
+                                    kvpid, order, arrive, err, dn);
     return hipGetLastError();
 }
 
@@ -609,11 +619,11 @@ hipError_t launch_resid_norm(float* h, const float* part, int S, int M, int d, f
 
 hipError_t launch_embed(const cdb_model_desc& md, const uint16_t* embed, const int32_t* tokens, const cdb_rows& r,
                         const cdb_kv& kv, const KvTarget& kt, int n_slots, float* h, float2* rope, int32_t* kvpid,
-                        int32_t* order, int* err, hipStream_t st) {
+                        int32_t* order, int* arrive, int* err, hipStream_t st) {
     if (r.n_rows <= 0) return hipSuccess;
     if (order && r.n_rows > kMaxRows) return hipErrorInvalidValue;
     k_embed<<<r.n_rows, 256, 0, st>>>(md.d, md.vocab, n_slots, kv.max_seqs, page_cap(kv), md.head_dim, md.rope_base,
-                                       embed, tokens, r.slot, r.seq, r.pos, h, rope, kt, kvpid, order, err,
+                                       embed, tokens, r.slot, r.seq, r.pos, h, rope, kt, kvpid, order, arrive, err,
                                        r.d_n_rows);
     return hipGetLastError();
 }
