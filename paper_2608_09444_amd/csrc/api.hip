@@ -55,33 +55,33 @@ struct ModelGemms {
     GemmShape qkv, o, gu, down, adapter, adapter_part, lm;
 };
 // Launch shapes of the model's projections for calls of M rows: the skinny
-// weight-streaming kernel up to kMaxRows rows, the tile kernel above.
-static ModelGemms model_gemms(const cdb_model_desc& d, int M = 0) {
+// weight-streaming kernel up to kMaxRows rows, whose sums do not depend on the
+// row count, as the mixed-depth batches need; the tile kernels above, and for
+// prefill chunks from fewer rows on, where they are faster (Ouro widths, skinny
+// -> tile): O and down from 65 rows (10.1 and 13.1 -> 6.5 and 11 us at 66 rows),
+// q/k/v and gate/up from 129 (25.9 and 43.8 -> 19.4 and 28.0 us at 130 rows; at
+// 100 rows the skinny kernel's 17 and 22 us are ahead).
+constexpr int kTileRows = 129, kTilePartialRows = 65;
+static ModelGemms model_gemms(const cdb_model_desc& d, int M, bool prefill) {
+    auto shape = [&](int N, int K, int epi) {
+        const bool tile = M > kMaxRows || (prefill && M >= (epi == EPI_PARTIAL ? kTilePartialRows : kTileRows));
+        return tile ? gemm_shape_mn(N, K, M, epi) : gemm_shape(N, K, epi, M);
+    };
     ModelGemms g;
-    if (M > kMaxRows) {
-        g.qkv = gemm_shape_mn(3 * d.d, d.d, M, EPI_QKV);
-        g.o = gemm_shape_mn(d.d, d.d, M, EPI_PARTIAL);
-        g.gu = gemm_shape_mn(2 * d.d_ff, d.d, M, EPI_SWIGLU);
-        g.down = gemm_shape_mn(d.d, d.d_ff, M, EPI_PARTIAL);
-        g.adapter = gemm_shape_mn(d.d, 2 * d.d, M, EPI_STORE);
-        g.adapter_part = g.adapter;  // the loop step never has more than kMaxRows rows
-        g.lm = gemm_shape_mn(d.vocab, d.d, M, EPI_STORE);
-        return g;
-    }
-    g.qkv = gemm_shape(3 * d.d, d.d, EPI_QKV, M);
-    g.o = gemm_shape(d.d, d.d, EPI_PARTIAL, M);
-    g.gu = gemm_shape(2 * d.d_ff, d.d, EPI_SWIGLU, M);
-    g.down = gemm_shape(d.d, d.d_ff, EPI_PARTIAL, M);
-    g.adapter = gemm_shape(d.d, 2 * d.d, EPI_STORE, M);
-    g.adapter_part = gemm_shape(d.d, 2 * d.d, EPI_PARTIAL, M);
-    g.lm = gemm_shape(d.vocab, d.d, EPI_STORE, M);
+    g.qkv = shape(3 * d.d, d.d, EPI_QKV);
+    g.o = shape(d.d, d.d, EPI_PARTIAL);
+    g.gu = shape(2 * d.d_ff, d.d, EPI_SWIGLU);
+    g.down = shape(d.d, d.d_ff, EPI_PARTIAL);
+    g.adapter = shape(d.d, 2 * d.d, EPI_STORE);
+    g.adapter_part = M > kMaxRows ? g.adapter : gemm_shape(d.d, 2 * d.d, EPI_PARTIAL, M);  // loop step only
+    g.lm = shape(d.vocab, d.d, EPI_STORE);
     return g;
 }
 
-WsLayout ws_layout(const cdb_model_desc& d, int rows) {
+WsLayout ws_layout(const cdb_model_desc& d, int rows, bool prefill) {
     WsLayout L;
     const size_t D = d.d, F = d.d_ff, M = rows, M32 = gemm_rows(rows);
-    const ModelGemms g = model_gemms(d, rows);
+    const ModelGemms g = model_gemms(d, rows, prefill);
     // split-K partials of O, down and the loop step's adapter
     const size_t part = (size_t)std::max({g.o.S, g.down.S, d.injection ? g.adapter_part.S : 0}) * D;
     size_t off = 0;
@@ -147,14 +147,14 @@ struct Ctx {
     AttnScratch asplit;  // arrive: NULL for calls of too many rows to split
 };
 
-static Ctx make_ctx(const cdb_model* model, void* ws, int rows) {
+static Ctx make_ctx(const cdb_model* model, void* ws, int rows, bool prefill = false) {
     Ctx c{};
     c.md = &model->desc;
     c.wb = static_cast<const unsigned char*>(model->packed);
     weight_layout(model->desc, &c.wl);
-    c.gm = model_gemms(model->desc, rows);
+    c.gm = model_gemms(model->desc, rows, prefill);
     c.ws = static_cast<unsigned char*>(ws);
-    c.L = ws_layout(model->desc, rows);
+    c.L = ws_layout(model->desc, rows, prefill);
     c.err = reinterpret_cast<int*>(c.ws + c.L.err);
     c.h = reinterpret_cast<float*>(c.ws + c.L.h);
     c.h_in = reinterpret_cast<float*>(c.ws + c.L.h_in);
@@ -275,7 +275,7 @@ static cdb_status check_common(const cdb_model* model, const cdb_kv* kv, const c
     if (rows->n_rows < 0 || state->n_slots < 0 || kv->max_seqs < 0 || kv->max_pages < 0) return CDB_ERR_INVALID_ARG;
     if (rows->n_rows > kMaxRows) return CDB_ERR_CAPACITY;
     if (rows->n_rows > 0 && (!rows->slot || !rows->seq || !rows->pos)) return CDB_ERR_INVALID_ARG;
-    if (ws_bytes < ws_layout(d, rows->n_rows).total) return CDB_ERR_CAPACITY;
+    if (ws_bytes < ws_layout(d, rows->n_rows, false).total) return CDB_ERR_CAPACITY;
     const int layers = stage == 0 ? d.n_prelude : (stage == 1 ? d.n_core : d.n_coda);
     if (layers > 0) {
         void* pool = stage == 0 ? kv->pre_pool : (stage == 1 ? kv->core_pool : kv->coda_pool);
@@ -337,8 +337,9 @@ size_t cdb_workspace_bytes(const cdb_model_desc* desc, int32_t max_rows) {
     if (!desc || !desc_supported(*desc) || max_rows < 0 || max_rows > kMaxPrefillRows) return 0;
     // the layout is not monotonic in the row count (the split-K factor of the
     // tile GEMM shrinks as its grid grows): the largest one up to max_rows
-    size_t n = ws_layout(*desc, 0).total;
-    for (int r = 1; r <= max_rows; ++r) n = std::max(n, ws_layout(*desc, r).total);
+    size_t n = ws_layout(*desc, 0, false).total;
+    for (int r = 1; r <= max_rows; ++r)
+        n = std::max({n, r <= kMaxRows ? ws_layout(*desc, r, false).total : 0, ws_layout(*desc, r, true).total});
     return n;
 }
 
@@ -464,7 +465,7 @@ cdb_status cdb_loop_step_noalloc(const cdb_model* model, const cdb_kv* kv, const
     if (!d_error || !model || !rows) return CDB_ERR_INVALID_ARG;
     if (!desc_supported(model->desc)) return CDB_ERR_UNSUPPORTED;
     if (rows->n_rows < 0) return CDB_ERR_INVALID_ARG;
-    if (rows->n_rows > kMaxRows || ws_layout(model->desc, rows->n_rows).base > kNoAllocLimit)
+    if (rows->n_rows > kMaxRows || ws_layout(model->desc, rows->n_rows, false).base > kNoAllocLimit)
         return CDB_ERR_CAPACITY;
     void* ws = device_scratch();
     if (!ws) return CDB_ERR_HIP;
@@ -510,9 +511,9 @@ cdb_status cdb_prefill(const cdb_model* model, const cdb_kv* kv, int32_t seq, in
         void* pool = stage == 0 ? kv->pre_pool : (stage == 1 ? kv->core_pool : kv->coda_pool);
         if (layers > 0 && !pool) return CDB_ERR_INVALID_ARG;
     }
-    if (ws_bytes < ws_layout(d, n_rows).total) return CDB_ERR_CAPACITY;
+    if (ws_bytes < ws_layout(d, n_rows, true).total) return CDB_ERR_CAPACITY;
     const int M = n_rows;
-    Ctx c = make_ctx(model, ws, M);
+    Ctx c = make_ctx(model, ws, M, true);
     const Chunk chunk{seq, pos0};
     cdb_rows r{M, c.prow, c.prow + M, c.prow + 2 * M, nullptr, nullptr, nullptr};
     HIPCHK(launch_prefill_rows(seq, pos0, M, c.prow, st));

@@ -100,8 +100,9 @@ struct EpiArgs {
 
 struct GemmShape {
     int N, K, S, KW;  // packed output columns, reduction length, K splits over workgroups, waves per workgroup
-    int NS;           // 32-column stripes per workgroup (1 or 2)
+    int NS;           // 32-column stripes per workgroup (1 or 2), or kTileShapes: the tile kernels
 };
+constexpr int kTileShapes = 4;
 
 // ---------------------------------------------------------------- layouts
 struct WeightLayout {
@@ -116,10 +117,10 @@ struct WsLayout {
     size_t base;  // bytes up to here; what follows speeds calls up but does not decide which calls are accepted
     size_t apart, arrive, total;
 };
-WsLayout ws_layout(const cdb_model_desc& d, int rows);
+WsLayout ws_layout(const cdb_model_desc& d, int rows, bool prefill);  // of a stage call, or of cdb_prefill
 
 GemmShape gemm_shape(int N, int K, int epi, int M);  // M <= kMaxRows
-GemmShape gemm_shape_mn(int N, int K, int M, int epi);  // M > kMaxRows
+GemmShape gemm_shape_mn(int N, int K, int M, int epi);  // tile kernels
 bool desc_supported(const cdb_model_desc& d);
 
 // ---------------------------------------------------------------- launchers

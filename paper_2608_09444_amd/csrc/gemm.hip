@@ -398,368 +398,373 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     stripe_epilogue<EPI>(fin, fld, nt, NS, mcap, s, tid, nthr, ga, ea, qs);
 }
 
-// q/k/v epilogue of a wave's (32 WM)-row x 64-column block (stripes nt0,
-// nt0 + 1; rows m0 .. m0 + 32 WM - 1) staged in LDS as fin[n][m - m0] (pitch
-// fld): each lane takes a run of consecutive dims of one row, so the stores
-// are 16-byte vectors (4 fp32 q values, or 8 bf16 K/V values) instead of one
-// column of 32 rows per instruction.  A q stripe gives a lane 4 WM runs (rows
-// lane/8 + 8i, 4 dims), a K/V stripe 2 WM runs (rows lane/4 + 16i, 8 dims).  The global loads
-// (RoPE factors, page ids, positions; qkv_block_loads) are issued before the
-// GEMM's main loop: the stores may alias them, so loads left between stores
-// would wait one by one.  Same arithmetic per element as epilogue_elem.
-struct QkvBlockInputs {
-    float4 rc[2][16];  // (cos, sin) pairs of each run, two per float4
-    int pid[2][4], tok[2][4];
+// Tile GEMM of prefill chunks.
+//
+// A workgroup owns a (32 WM)-row x (32 WN)-column output tile and one K split;
+// its 4 waves (one per SIMD, up to 512 registers each) split that K range and
+// each accumulates the whole tile, so every operand tile is fetched exactly
+// once per workgroup, straight into registers: no LDS staging, no barrier in
+// the loop, and up to 8 k steps of WM + WN KiB per wave in flight (200 KiB per
+// CU).  What bounds these shapes is the operand stream into a CU (L2 hits reach
+// 130 KB per us and CU, of which WM x WN = 4 x 3 tiles need 7 KiB per 12 MFMAs)
+// and the launch and epilogue around a loop of 10-15 us; a 32 KiB two-stage LDS
+// ring kept too few bytes in flight.  The waves' tiles are then exchanged
+// through LDS (wave w sums m-tile w, in wave order) and the epilogue runs from
+// the accumulators: lane l holds row l % 32 and, for each j, column (j/4)*8 +
+// (l/32)*4 + j%4, so 4 consecutive j are 4 consecutive columns, and the RoPE /
+// SwiGLU partner of element j is j ^ 8.
+//
+// Against the kernel of 2 x 2 waves that each fetched their own operands, Ouro
+// widths at 512 rows: q/k/v 35.4 -> 23.8 us, O 12.9 -> 11.5, down 24.6 -> 21.9;
+// at 333 rows q/k/v 34.9 -> 22.8; Huginn widths at 300 rows: q/k/v 135 -> 95,
+// O 40 -> 36, down 124 -> 104, adapter 141 -> 84.
+//
+// Tile order: the dispatcher hands workgroup b to XCD b % 8, so each XCD takes
+// a contiguous range of tasks, row tile first: the row tiles that read one
+// weight tile run together on one XCD and share its L2.
+struct TileShape {
+    int WM, WN, gx, gy, S;  // m-tiles and stripes per workgroup, column and row groups, K splits
 };
 
-template <int WM>
-__device__ __forceinline__ void qkv_block_loads(QkvBlockInputs& in, int nt0, int stripes, int m0, int M, int lane,
-                                                const EpiArgs& ea) {
-    const int gph = ea.hd >> 5, hg = ea.H * gph, half_hd = ea.hd >> 1;
-    float4 (&rc)[2][16] = in.rc;
-    int (&pid)[2][4] = in.pid;
-    int (&tok)[2][4] = in.tok;
+__host__ __device__ constexpr int tile_depth(int WM, int WN) { return 200 / (4 * (WM + WN)) < 8 ? 200 / (4 * (WM + WN)) : 8; }
+
+template <int EPI, int WM, int WN>
+__device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, int nt0, int split, int lane,
+                                              const GemmArgs& ga, const EpiArgs& ea) {
+    const int stripes = ga.N >> 5, half = lane >> 5;
+    if (EPI == EPI_QKV) {
+        const int gph = ea.hd >> 5, hg = ea.H * gph, half_hd = ea.hd >> 1;
+        const int mc = min(m, ga.M - 1);
+        const int pid = ea.kvpid[mc], tok = ea.pos[mc] % kPage;
+        // the row's RoPE factors first: the stores may alias them
+        float4 cs[WN][4];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int g = nt0 + a;
-        if (g >= stripes) break;
-        const int part = g / hg, gi = (g - part * hg) % gph;
-        if (part == 0) {
+        for (int a = 0; a < WN; ++a) {
+            const int gi = (min(nt0 + a, stripes - 1) % hg) % gph;
+            const float2* r = ea.rope + (size_t)mc * half_hd + gi * 16 + half * 4;
 #pragma unroll
-            for (int it = 0; it < 4 * WM; ++it) {
-                const int m = min(m0 + (lane >> 3) + 8 * it, M - 1);
-                const float4* cs = reinterpret_cast<const float4*>(ea.rope + (size_t)m * half_hd + gi * 16 + (lane & 3) * 4);
-                rc[a][2 * it] = cs[0];
-                rc[a][2 * it + 1] = cs[1];
-            }
-        } else {
-#pragma unroll
-            for (int it = 0; it < 2 * WM; ++it) {
-                const int m = min(m0 + (lane >> 2) + 16 * it, M - 1);
-                pid[a][it] = ea.kvpid[m];
-                tok[a][it] = ea.pos[m] % kPage;
-                if (part == 1) {
-                    const float4* cs = reinterpret_cast<const float4*>(ea.rope + (size_t)m * half_hd + gi * 16 + (lane & 1) * 8);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) rc[a][4 * it + i] = cs[i];
-                }
+            for (int u = 0; u < 2; ++u) {
+                cs[a][2 * u] = *reinterpret_cast<const float4*>(r + u * 8);
+                cs[a][2 * u + 1] = *reinterpret_cast<const float4*>(r + u * 8 + 2);
             }
         }
-    }
-}
-
-template <int WM>
-__device__ __forceinline__ void qkv_block_epilogue(const QkvBlockInputs& in, const float* fin, int fld, int nt0,
-                                                   int stripes, int m0, int M, int lane, const EpiArgs& ea) {
-    const int gph = ea.hd >> 5, hg = ea.H * gph, half_hd = ea.hd >> 1;
-    const float4 (&rc)[2][16] = in.rc;
-    const int (&pid)[2][4] = in.pid;
-    const int (&tok)[2][4] = in.tok;
-    // pair t of a run from its float4s
-    auto cpair = [](const float4* r, int t) {
-        const float4 v = r[t >> 1];
-        return (t & 1) ? make_float2(v.z, v.w) : make_float2(v.x, v.y);
-    };
+        if (m >= ga.M) return;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int g = nt0 + a;
-        if (g >= stripes) break;
-        const int part = g / hg, rem = g - part * hg;
-        const int head = rem / gph, gi = rem - head * gph;
-        const float* f = fin + a * 32 * fld;
-        if (part == 0) {
+        for (int a = 0; a < WN; ++a) {
+            const int g = nt0 + a;
+            if (g >= stripes) break;
+            const int part = g / hg, rem = g - part * hg;
+            const int head = rem / gph, gi = rem - head * gph;
 #pragma unroll
-            for (int it = 0; it < 4 * WM; ++it) {
-                const int ml = (lane >> 3) + 8 * it, half = (lane >> 2) & 1, j4 = (lane & 3) * 4;
-                const int m = m0 + ml;
-                if (m >= M) continue;
-                float o[4];
+            for (int u = 0; u < 2; ++u) {  // pairs jj = 8u + 4 half + 0..3 of the stripe's 16
+                float lo[4], hi[4];
+                const float c[8] = {cs[a][2 * u].x, cs[a][2 * u].y, cs[a][2 * u].z, cs[a][2 * u].w,
+                                    cs[a][2 * u + 1].x, cs[a][2 * u + 1].y, cs[a][2 * u + 1].z, cs[a][2 * u + 1].w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int jj = j4 + i;
-                    const float val = f[(half * 16 + jj) * fld + ml], partner = f[((half ^ 1) * 16 + jj) * fld + ml];
-                    const float2 c = cpair(&rc[a][2 * it], i);
-                    const float xf = half ? partner : val, xs = half ? val : partner;
-                    o[i] = half ? (xs * c.x + xf * c.y) : (xf * c.x - xs * c.y);
+                    const float xf = acc[a][u * 4 + i], xs = acc[a][8 + u * 4 + i];
+                    lo[i] = part < 2 ? xf * c[2 * i] - xs * c[2 * i + 1] : xf;
+                    hi[i] = part < 2 ? xs * c[2 * i] + xf * c[2 * i + 1] : xs;
                 }
-                float* dst = ea.q + (size_t)m * (ea.H * ea.hd) + head * ea.hd + gi * 16 + j4 + half * half_hd;
-                *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
+                const int dim = gi * 16 + u * 8 + half * 4;
+                if (part == 0) {
+                    float* dst = ea.q + (size_t)m * (ea.H * ea.hd) + head * ea.hd + dim;
+                    *reinterpret_cast<float4*>(dst) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+                    *reinterpret_cast<float4*>(dst + half_hd) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+                } else if (pid >= 0) {  // -1: unmapped (reported by the row-entry kernel)
+                    const KvTarget& kv = ea.kv;
+                    uint16_t* dst = kv.pool + kv_offset(kv.layer, pid, kv.n_pages, part - 1, head, ea.H, tok, ea.hd) + dim;
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]));
+                    *reinterpret_cast<uint2*>(dst + half_hd) = make_uint2(pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3]));
+                }
+            }
+        }
+        return;
+    }
+    if (m >= ga.M) return;
+#pragma unroll
+    for (int a = 0; a < WN; ++a) {
+        if (nt0 + a >= stripes) break;
+        if (EPI == EPI_SWIGLU) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float g = acc[a][u * 4 + i];
+                    v[i] = g / (1.0f + __expf(-g)) * acc[a][8 + u * 4 + i];
+                }
+                const int f = (nt0 + a) * 16 + u * 8 + half * 4;
+                *reinterpret_cast<uint2*>(ea.act + frag_index(m, f, ea.ld_act)) =
+                    make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
             }
         } else {
+            // N and the row pitch are multiples of 32 floats
+            float* dst = (EPI == EPI_PARTIAL ? ga.part + ((size_t)split * ga.M + m) * ga.N : ea.out + (size_t)m * ea.ld_out) +
+                         (nt0 + a) * 32 + half * 4;
 #pragma unroll
-            for (int it = 0; it < 2 * WM; ++it) {
-                const int ml = (lane >> 2) + 16 * it, half = (lane >> 1) & 1, j8 = (lane & 1) * 8;
-                const int m = m0 + ml;
-                // pid -1: unmapped (reported by the row-entry kernel)
-                if (m >= M || pid[a][it] < 0) continue;
-                uint32_t w[4];
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    float o2[2];
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        const int jj = j8 + i + b;
-                        const float val = f[(half * 16 + jj) * fld + ml];
-                        float outv = val;
-                        if (part == 1) {
-                            const float partner = f[((half ^ 1) * 16 + jj) * fld + ml];
-                            const float2 c = cpair(&rc[a][4 * it], i + b);
-                            const float xf = half ? partner : val, xs = half ? val : partner;
-                            outv = half ? (xs * c.x + xf * c.y) : (xf * c.x - xs * c.y);
-                        }
-                        o2[b] = outv;
-                    }
-                    w[i / 2] = pack_bf16(o2[0], o2[1]);
-                }
-                const KvTarget& kv = ea.kv;
-                uint16_t* dst = kv.pool + kv_offset(kv.layer, pid[a][it], kv.n_pages, part - 1, head, ea.H, tok[a][it], ea.hd) +
-                                gi * 16 + j8 + half * half_hd;
-                *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
-            }
+            for (int u = 0; u < 4; ++u)
+                *reinterpret_cast<float4*>(dst + u * 8) =
+                    make_float4(acc[a][u * 4], acc[a][u * 4 + 1], acc[a][u * 4 + 2], acc[a][u * 4 + 3]);
         }
     }
 }
 
-// Large-M GEMM (prefill chunks of up to 512 rows), where the product is
-// compute-bound (about M FLOP per weight byte).  A workgroup owns a
-// (64 WM)-row x 128-column output tile and one K split: 4 waves in 2 x 2, each
-// 32 WM rows x 64 columns (WM m-tiles x 2 stripes, 2 WM MFMAs per 16-wide k
-// step), operands read straight from the packed weights and the fragment-
-// layout activations (each tile feeds two waves; the second read is served by
-// the caches), double-buffered in registers.  Each wave owns its outputs, so
-// the epilogue runs from the accumulators: column n's RoPE / SwiGLU partner
-// n ^ 16 is element j ^ 8 of the same lane.
+// floats of LDS of the exchange: every wave's stripes of the m-tiles it does not sum
+__host__ __device__ constexpr int tile_exchange_stripes(int WM, int WN) {
+    return 4 * WM * WN * 1024 * 4 <= 160 * 1024 ? WN : (WN + 1) / 2;
+}
+
+template <int EPI, int WM, int WN>
+__global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, TileShape ts) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int KS = ga.K >> 4, stripes = ga.N >> 5;
+    const int mtiles = gemm_rows(ga.M) >> 5;  // m-tiles the activation buffer holds
+    const int tasks = ts.gx * ts.gy * ts.S, per = (tasks + 7) / 8;
+    const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || t >= tasks) return;
+    const int by = t % ts.gy, s = (t / ts.gy) % ts.S, bx = t / (ts.gy * ts.S);
+    const int a0 = (int)(((long)s * KS) / ts.S), a1 = (int)(((long)(s + 1) * KS) / ts.S);
+    const int k0 = a0 + (wave * (a1 - a0)) / 4, k1 = a0 + ((wave + 1) * (a1 - a0)) / 4;
+    const int nt0 = bx * WN, mt0 = by * WM;
+
+    floatx16 acc[WM][WN];
+#pragma unroll
+    for (int b = 0; b < WM; ++b)
+#pragma unroll
+        for (int a = 0; a < WN; ++a)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[b][a][j] = 0.f;
+
+    // tiles past the matrix re-read the last one (their results are not stored)
+    const u32x4* wsrc[WN];
+    const u32x4* xsrc[WM];
+#pragma unroll
+    for (int a = 0; a < WN; ++a)
+        wsrc[a] = reinterpret_cast<const u32x4*>(ga.Wp) + (size_t)min(nt0 + a, stripes - 1) * KS * 64;
+#pragma unroll
+    for (int b = 0; b < WM; ++b)
+        xsrc[b] = reinterpret_cast<const u32x4*>(ga.X) + (size_t)min(mt0 + b, mtiles - 1) * KS * 64;
+    constexpr int D = tile_depth(WM, WN);
+    u32x4 w[D][WN], x[D][WM];
+    auto load = [&](int i, int ks) {
+#pragma unroll
+        for (int a = 0; a < WN; ++a) w[i][a] = wsrc[a][(size_t)ks * 64 + lane];
+#pragma unroll
+        for (int b = 0; b < WM; ++b) x[i][b] = xsrc[b][(size_t)ks * 64 + lane];
+    };
+    auto mma = [&](int i) {
+#pragma unroll
+        for (int b = 0; b < WM; ++b)
+#pragma unroll
+            for (int a = 0; a < WN; ++a)
+                acc[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[i][a]),
+                                                                    __builtin_bit_cast(bf16x8, x[i][b]), acc[b][a], 0, 0, 0);
+    };
+    // groups of D k steps: a slot's next load is issued as soon as its MFMAs are
+    const int n = k1 - k0, groups = n / D, rem = n - groups * D;
+    int ks = k0;
+    if (groups > 0) {
+#pragma unroll
+        for (int i = 0; i < D; ++i) load(i, ks + i);
+        for (int g = 1; g < groups; ++g, ks += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                mma(i);
+                load(i, ks + D + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            mma(i);
+            if (i < rem) load(i, ks + D + i);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (i < rem) load(i, ks + i);
+    }
+#pragma unroll
+    for (int i = 0; i < D - 1; ++i)
+        if (i < rem) mma(i);
+
+    // exchange: wave v's copy of (m-tile b, stripe a), in lane order
+    extern __shared__ __align__(16) float smem[];
+    constexpr int EX = tile_exchange_stripes(WM, WN);
+    floatx16 sum[WN];
+#pragma unroll
+    for (int r = 0; r < WN; r += EX) {
+        if (r > 0) __syncthreads();  // the round before has been read
+        constexpr int NE = EX;
+#pragma unroll
+        for (int b = 0; b < WM; ++b)
+#pragma unroll
+            for (int a = r; a < r + NE && a < WN; ++a) {
+                float4* dst = reinterpret_cast<float4*>(smem) + (size_t)((wave * WM + b) * NE + a - r) * 256 + lane;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    dst[u * 64] = make_float4(acc[b][a][u * 4], acc[b][a][u * 4 + 1], acc[b][a][u * 4 + 2], acc[b][a][u * 4 + 3]);
+            }
+        __syncthreads();
+        if (wave < WM) {
+#pragma unroll
+            for (int a = r; a < r + NE && a < WN; ++a)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int src = 0; src < 4; ++src) {
+                        const float4 p = reinterpret_cast<const float4*>(smem)[(size_t)((src * WM + wave) * NE + a - r) * 256 + u * 64 + lane];
+                        v.x += p.x;
+                        v.y += p.y;
+                        v.z += p.z;
+                        v.w += p.w;
+                    }
+                    sum[a][u * 4] = v.x;
+                    sum[a][u * 4 + 1] = v.y;
+                    sum[a][u * 4 + 2] = v.z;
+                    sum[a][u * 4 + 3] = v.w;
+                }
+        }
+    }
+    if (wave < WM) tile_epilogue<EPI, WM, WN>(sum, (mt0 + wave) * 32 + (lane & 31), nt0, s, lane, ga, ea);
+}
+
+// Tile GEMM staged through LDS, for gate/up and full-width LM heads above 256
+// rows: (64 WM)-row x 128-column tiles, 4 waves in 2 x 2, each 32 WM rows x 64
+// columns.  Their grids take more than one round of k_gemm_tile's workgroups
+// (one per CU), where two smaller ones per CU overlap one's start and epilogue
+// with the other's loop: Ouro-shaped gate/up at 512 rows 36 us against 40,
+// Huginn-shaped at 300 rows 183 against 217, LM heads 113 against 128 and 339
+// against 365.
 //
-// Tile order (xcd_order): the grid is one-dimensional, padded to a multiple of
-// 8, and the dispatcher hands workgroup b to XCD b % 8.  With xcd_order 0 the
-// tasks run column group first (every row tile of a column group lands on a
-// different XCD); with 1 each XCD takes a contiguous range of tasks ordered
-// row tile first, so the row tiles that read one weight tile run together on
-// one XCD and share its L2.
-template <int EPI, bool LDS, int WM>
-__global__ __launch_bounds__(256) void k_gemm_mn(GemmArgs ga, EpiArgs ea, int xcd_order) {
+// xcd_order: the tasks of an XCD are a contiguous range, row tile first (used
+// for grids of more than two workgroups per CU), else column group first.
+template <int EPI, int WM>
+__global__ __launch_bounds__(256) void k_gemm_lds(GemmArgs ga, EpiArgs ea, int xcd_order) {
     static_assert(WM == 1 || WM == 2, "one or two m-tiles per wave");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = ga.K >> 4;
     const int stripes = ga.N >> 5;
-    const int mtiles = (gemm_rows(ga.M) + 31) >> 5;  // m-tiles the activation buffer holds
-    const int gx = (stripes + 3) / 4, gy = (ga.M + 64 * WM - 1) / (64 * WM), tasks = gx * gy * ga.S;
-    int bx, by, s;
+    const int mtiles = gemm_rows(ga.M) >> 5;  // m-tiles the activation buffer holds
+    const int gx = (stripes + 3) / 4, gy = (ga.M + 64 * WM - 1) / (64 * WM), tasks = gx * gy;
+    int bx, by;
     if (xcd_order) {
         const int per = (tasks + 7) / 8;
         const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
         if (t >= tasks) return;
         by = t % gy;
-        s = (t / gy) % ga.S;
-        bx = t / (gy * ga.S);
+        bx = t / gy;
     } else {
         const int t = blockIdx.x;
         if (t >= tasks) return;
         bx = t % gx;
-        by = (t / gx) % gy;
-        s = t / (gx * gy);
+        by = t / gx;
     }
-    const int k0 = (int)(((long)s * KS) / ga.S), k1 = (int)(((long)(s + 1) * KS) / ga.S);
     const int nt0 = bx * 4 + (wave & 1) * 2;   // first stripe of this wave
     const int mt0 = by * 2 * WM + (wave >> 1) * WM;  // first m-tile of this wave
 
-    floatx16 acc[2][WM];
+    floatx16 acc[WM][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < WM; ++b)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[a][b][j] = 0.f;
-    QkvBlockInputs qin;
-    if constexpr (EPI == EPI_QKV) qkv_block_loads<WM>(qin, nt0, stripes, mt0 * 32, ga.M, lane, ea);
-
-    if constexpr (!LDS) {
-        // tiles past the matrix re-read the last one (their results are not stored)
-        const u32x4* wsrc[2];
-        const u32x4* xsrc[WM];
-    #pragma unroll
-        for (int a = 0; a < 2; ++a)
-            wsrc[a] = reinterpret_cast<const u32x4*>(ga.Wp) + (size_t)min(nt0 + a, stripes - 1) * KS * 64 + lane;
-    #pragma unroll
-        for (int b = 0; b < WM; ++b)
-            xsrc[b] = reinterpret_cast<const u32x4*>(ga.X) + (size_t)min(mt0 + b, mtiles - 1) * KS * 64 + lane;
-        constexpr int CH = 4;
-        u32x4 wa[CH][2], wb[CH][2], xa[CH][WM], xb[CH][WM];
-        auto load = [&](u32x4 (&w)[CH][2], u32x4 (&x)[CH][WM], int c0) {
-    #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const int ks = min(c0 + i, k1 - 1);
-    #pragma unroll
-                for (int a = 0; a < 2; ++a) w[i][a] = wsrc[a][(size_t)ks * 64];
-    #pragma unroll
-                for (int b = 0; b < WM; ++b) x[i][b] = xsrc[b][(size_t)ks * 64];
-            }
-        };
-        auto compute = [&](const u32x4 (&w)[CH][2], const u32x4 (&x)[CH][WM], int c0) {
-    #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const uint32_t keep = c0 + i < k1 ? 0xffffffffu : 0u;
-    #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const bf16x8 wv = __builtin_bit_cast(bf16x8, w[i][a] & keep);
-    #pragma unroll
-                    for (int b = 0; b < WM; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(bf16x8, x[i][b]),
-                                                                            acc[a][b], 0, 0, 0);
-                }
-            }
-        };
-        if (k0 < k1) load(wa, xa, k0);
-        for (int c0 = k0; c0 < k1; c0 += 2 * CH) {
-            if (c0 + CH < k1) load(wb, xb, c0 + CH);
-            compute(wa, xa, c0);
-            if (c0 + 2 * CH < k1) load(wa, xa, c0 + 2 * CH);
-            if (c0 + CH < k1) compute(wb, xb, c0 + CH);
+            for (int j = 0; j < 16; ++j) acc[b][a][j] = 0.f;
+    // LDS ring of 2 stages of 4 k steps: a stage holds the workgroup's 4
+    // weight tiles and 2 WM activation tiles of each k step (1 KiB each,
+    // lane order), copied global -> LDS by the waves with direct loads (tile
+    // i of a stage by wave i % 4); each wave then reads its 2 + WM operands
+    // per k step
+    constexpr int CH = 4, NBUF = 2;
+    constexpr int TPK = 4 + 2 * WM;  // tiles per k step
+    constexpr int TPS = CH * TPK;    // tiles per stage
+    constexpr int LPW = TPS / 4;     // loads per wave per stage
+    static_assert(TPS % 4 == 0, "a stage's tiles split evenly over the 4 waves");
+    extern __shared__ __align__(16) unsigned char lds_ring[];
+    const int ntb = bx * 4, mtb = by * 2 * WM;
+    const u32x4* Wg = reinterpret_cast<const u32x4*>(ga.Wp);
+    const u32x4* Xg = reinterpret_cast<const u32x4*>(ga.X);
+    const int nst = (KS + CH - 1) / CH;
+    auto issue = [&](int st) {
+        unsigned char* base = lds_ring + (size_t)(st % NBUF) * TPS * 1024;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int t = wave + 4 * i;  // tile within the stage
+            const int kk = t / TPK, slot = t - kk * TPK;
+            const int ks = min(st * CH + kk, KS - 1);
+            const u32x4* src = slot < 4 ? Wg + ((size_t)min(ntb + slot, stripes - 1) * KS + ks) * 64
+                                        : Xg + ((size_t)min(mtb + slot - 4, mtiles - 1) * KS + ks) * 64;
+            __builtin_amdgcn_global_load_lds(src + lane, (__attribute__((address_space(3))) void*)(base + t * 1024),
+                                             16, 0, 0);
         }
-    } else {
-        // LDS ring of 2 stages of 4 k steps: a stage holds the workgroup's 4
-        // weight tiles and 2 WM activation tiles of each k step (1 KiB each,
-        // lane order), copied global -> LDS by the waves with direct loads (tile
-        // i of a stage by wave i % 4); each wave then reads its 2 + WM operands
-        // per k step
-        constexpr int CH = 4, NBUF = 2;
-        constexpr int TPK = 4 + 2 * WM;  // tiles per k step
-        constexpr int TPS = CH * TPK;    // tiles per stage
-        constexpr int LPW = TPS / 4;     // loads per wave per stage
-        static_assert(TPS % 4 == 0, "a stage's tiles split evenly over the 4 waves");
-        extern __shared__ __align__(16) unsigned char lds_ring[];
-        const int ntb = bx * 4, mtb = by * 2 * WM;
-        const u32x4* Wg = reinterpret_cast<const u32x4*>(ga.Wp);
-        const u32x4* Xg = reinterpret_cast<const u32x4*>(ga.X);
-        const int nst = (k1 - k0 + CH - 1) / CH;
-        auto issue = [&](int st) {
-            unsigned char* base = lds_ring + (size_t)(st % NBUF) * TPS * 1024;
+    };
+    if (nst > 0) issue(0);
+    const int wn = wave & 1, wm = wave >> 1;
+    for (int st = 0; st < nst; ++st) {
+        // this wave's loads of stage st are done; the barrier covers the
+        // other waves' loads and every wave's reads of the stage refilled next
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        if (st + 1 < nst) issue(st + 1);
+        const unsigned char* base = lds_ring + (size_t)(st % NBUF) * TPS * 1024 + lane * 16;
 #pragma unroll
-            for (int i = 0; i < LPW; ++i) {
-                const int t = wave + 4 * i;  // tile within the stage
-                const int kk = t / TPK, slot = t - kk * TPK;
-                const int ks = min(k0 + st * CH + kk, k1 - 1);
-                const u32x4* src = slot < 4 ? Wg + ((size_t)min(ntb + slot, stripes - 1) * KS + ks) * 64
-                                            : Xg + ((size_t)min(mtb + slot - 4, mtiles - 1) * KS + ks) * 64;
-                __builtin_amdgcn_global_load_lds(src + lane, (__attribute__((address_space(3))) void*)(base + t * 1024),
-                                                 16, 0, 0);
-            }
-        };
-        if (nst > 0) issue(0);
-        const int wn = wave & 1, wm = wave >> 1;
-        for (int st = 0; st < nst; ++st) {
-            // this wave's loads of stage st are done; the barrier covers the
-            // other waves' loads and every wave's reads of the stage refilled next
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            if (st + 1 < nst) issue(st + 1);
-            const unsigned char* base = lds_ring + (size_t)(st % NBUF) * TPS * 1024 + lane * 16;
+        for (int i = 0; i < CH; ++i) {
+            const uint32_t keep = st * CH + i < KS ? 0xffffffffu : 0u;
+            u32x4 w[2], x[WM];
 #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const uint32_t keep = k0 + st * CH + i < k1 ? 0xffffffffu : 0u;
-                u32x4 w[2], x[WM];
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-                    w[a] = *reinterpret_cast<const u32x4*>(base + (i * TPK + wn * 2 + a) * 1024);
-#pragma unroll
-                for (int b = 0; b < WM; ++b)
-                    x[b] = *reinterpret_cast<const u32x4*>(base + (i * TPK + 4 + wm * WM + b) * 1024);
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const bf16x8 wv = __builtin_bit_cast(bf16x8, w[a] & keep);
-#pragma unroll
-                    for (int b = 0; b < WM; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(bf16x8, x[b]),
-                                                                            acc[a][b], 0, 0, 0);
-                }
-            }
-        }
-    }
-    if constexpr (EPI == EPI_QKV) {
-        // the wave's block through its own LDS region (64 columns x (32 WM + 1)-float rows);
-        // on the LDS path the region overlaps the ring, which the other waves may still be reading
-        if constexpr (LDS) __syncthreads();
-        extern __shared__ __align__(16) unsigned char lds_ring[];
-        constexpr int fld = 32 * WM + 1;
-        float* fin = reinterpret_cast<float*>(lds_ring) + wave * 64 * fld;
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
+            for (int a = 0; a < 2; ++a)
+                w[a] = *reinterpret_cast<const u32x4*>(base + (i * TPK + wn * 2 + a) * 1024);
 #pragma unroll
             for (int b = 0; b < WM; ++b)
+                x[b] = *reinterpret_cast<const u32x4*>(base + (i * TPK + 4 + wm * WM + b) * 1024);
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int n = a * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
-                    fin[n * fld + b * 32 + (lane & 31)] = acc[a][b][j];
-                }
-        qkv_block_epilogue<WM>(qin, fin, fld, nt0, stripes, mt0 * 32, ga.M, lane, ea);
-        return;
-    }
-    const QkvStage qs{};
+            for (int a = 0; a < 2; ++a) {
+                const bf16x8 wv = __builtin_bit_cast(bf16x8, w[a] & keep);
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        if (nt0 + a >= stripes) continue;
-#pragma unroll
-        for (int b = 0; b < WM; ++b) {
-            const int m = (mt0 + b) * 32 + (lane & 31);
-            if (m >= ga.M) continue;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int n = (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
-                epilogue_elem<EPI>(acc[a][b][j], acc[a][b][j ^ 8], m, (nt0 + a) * 32 + n, s, ga, ea, qs);
+                for (int b = 0; b < WM; ++b)
+                    acc[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(bf16x8, x[b]),
+                                                                        acc[b][a], 0, 0, 0);
             }
         }
     }
+#pragma unroll
+    for (int b = 0; b < WM; ++b)
+        tile_epilogue<EPI, WM, 2>(acc[b], (mt0 + b) * 32 + (lane & 31), nt0, 0, lane, ga, ea);
 }
 
-// Which tile-kernel path a projection takes: the LDS-staged one pays off for
-// the wide projections (gate/up and a full-width LM head: 20% faster at 512
-// rows) and for split-K projections whose splits run long k loops (Huginn-
-// shaped O and down, 165 and 560 k steps per split at 512 rows: 64 -> 52 and
-// 218 -> 174 us); q/k/v and the short-split O and down (Ouro-shaped: 32 and 88
-// k steps) are faster with direct loads.
-static int mn_splits(int N, int K, int M, int rows_per_tile);
+// Which projections above 256 rows take the LDS-staged kernel (see there).
+static bool lds_tiles(int epi, int N) { return epi == EPI_SWIGLU || (epi == EPI_STORE && N >= 8192); }
+// m-tiles per wave of that kernel: 1 where the rows span an odd number of
+// 64-row tiles, which 128-row tiles would pad by 64 rows (gate/up at 300 rows:
+// 36.0 -> 30.1 us; at 512 rows 64-row tiles gain nothing).
 static int lds_wave_mtiles(int M) { return ((M + 63) / 64) % 2 ? 1 : 2; }
-static bool mn_lds(int epi, int N, int K, int M) {
-    if (epi == EPI_SWIGLU || (epi == EPI_STORE && N >= 8192)) return true;
-    return epi == EPI_PARTIAL && (K / 16) / mn_splits(N, K, M, 64 * lds_wave_mtiles(M)) >= 128;
+
+// Launch shape of the tile kernel.  Row groups of 3 or 4 m-tiles, whichever
+// pads fewer; 2 (split-K epilogue only), 3 or 4 stripes and the K splits by the
+// rounds that the grid takes on the 256 CUs (a workgroup fills one), each
+// costing its k steps per wave and a fixed part (in KiB of operands), plus the
+// split partials' trip through memory.
+static TileShape tile_shape(int N, int K, int M, int epi) {
+    const int mt = (M + 31) / 32, gy = (mt + 3) / 4, WM = (mt + gy - 1) / gy, stripes = N / 32, KS = K / 16;
+    TileShape best{};
+    double cost = 1e30;
+    for (int WN = epi == EPI_PARTIAL ? 2 : 3; WN <= (WM == 4 ? 3 : 4); ++WN)  // (4 x 4 tiles exceed the register file)
+        for (int S = 1; S <= (epi == EPI_PARTIAL ? 8 : 1); ++S) {
+            if (S > 1 && KS / S < 32) break;
+            const int gx = (stripes + WN - 1) / WN, rounds = (gx * gy * S + 255) / 256;
+            const double steps = (double)((KS + S - 1) / S + 3) / 4;
+            const double c = rounds * (steps * (WM + WN) + 100) + 70.0 * (S - 1) * ((double)M * N / (1 << 20));
+            if (c < cost) {
+                cost = c;
+                best = TileShape{WM, WN, gx, gy, S};
+            }
+        }
+    return best;
 }
 
-// m-tiles per wave of the tile kernel: 2 (128-row workgroup tiles) or 1 (64-row
-// tiles; the sums are the same either way).  Direct loads: 1 for q/k/v when
-// that grid still runs in one round on the 256 CUs; its workgroups take one
-// CU each (register bound), so at 257-320 rows of the Ouro-shaped q/k/v the
-// 64-row tiles use 240 CUs instead of 144 (29 -> 22 us); above that they would
-// take two rounds.  O and down are as fast or faster with 128-row tiles at
-// every size from 272 to 512 rows but 480-512.  LDS-staged: 1 when the rows
-// span an odd number of 64-row tiles, which 128-row tiles would pad by 64 rows
-// (gate/up at 300 rows: 36.0 -> 30.1 us; at 512 rows 64-row tiles gain nothing).
-static int mn_wave_mtiles(int epi, int N, int K, int M) {
-    if (mn_lds(epi, N, K, M)) return lds_wave_mtiles(M);
-    return epi == EPI_QKV && ((M + 63) / 64) * ((N / 32 + 3) / 4) <= 256 ? 1 : 2;
-}
-
-// K splits of the split-K partial epilogue: doubled until the grid covers the
-// chip, keeping at least 32 k steps per split.
-static int mn_splits(int N, int K, int M, int rows_per_tile) {
-    const int tiles = ((N / 32 + 3) / 4) * ((M + rows_per_tile - 1) / rows_per_tile);
-    const int KS = K / 16;
-    int S = 1;
-    while (tiles * S < 256 && KS / (S * 2) >= 32) S *= 2;
-    return S;
-}
-
-// Launch shape for M > kMaxRows rows (k_gemm_mn): K split only for the
-// split-K partial epilogue.
-GemmShape gemm_shape_mn(int N, int K, int M, int epi) {
-    const int S = epi == EPI_PARTIAL ? mn_splits(N, K, M, 64 * mn_wave_mtiles(epi, N, K, M)) : 1;
-    return GemmShape{N, K, S, 4, 4};
-}
-
-// XCD-aware tile order (see k_gemm_mn) for grids of more than two workgroups
-// per CU (LM heads and Huginn-shaped gate/up at 512 rows: 615 -> 485 and
-// 325 -> 292 us) and for LDS-staged split-K grids; the others keep the plain
-// order, which is as fast or up to 5% faster for them.
-static int mn_xcd_order(bool lds, int tasks, int S) { return tasks > 512 || (lds && S > 1) ? 1 : 0; }
+GemmShape gemm_shape_mn(int N, int K, int M, int epi) { return GemmShape{N, K, tile_shape(N, K, M, epi).S, 4, kTileShapes}; }
 
 GemmShape gemm_shape(int N, int K, int epi, int M) {
     // S and KW fix every wave's K range and so the summation order of each
@@ -847,34 +852,53 @@ static hipError_t launch_epi(const GemmArgs& ga, const EpiArgs& ea, int ns, hipS
     return ns == 2 ? launch_ns<EPI, 2>(ga, ea, st) : launch_ns<EPI, 1>(ga, ea, st);
 }
 
-template <int EPI, bool LDS, int WM>
-static hipError_t launch_mn_wm(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
-    const int tasks = (ga.N / 32 + 3) / 4 * ((ga.M + 64 * WM - 1) / (64 * WM)) * ga.S;
-    const dim3 grid((tasks + 7) / 8 * 8);
-    // dynamic LDS: the ring of the LDS path, the q/k/v epilogue's staging blocks
-    constexpr size_t ring = LDS ? 2 * 4 * (4 + 2 * WM) * 1024 : 0;
-    constexpr size_t stage = EPI == EPI_QKV ? 4 * 64 * (32 * WM + 1) * 4 : 0;
-    constexpr size_t smem = ring > stage ? ring : stage;
-    if constexpr (smem > 0) {
-        static bool attr_set = false;
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mn<EPI, LDS, WM>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
+template <int EPI, int WM>
+static hipError_t launch_lds_wm(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
+    const int tasks = (ga.N / 32 + 3) / 4 * ((ga.M + 64 * WM - 1) / (64 * WM));
+    constexpr size_t ring = 2 * 4 * (4 + 2 * WM) * 1024;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_lds<EPI, WM>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring);
+        if (e != hipSuccess) return e;
+        attr_set = true;
     }
-    k_gemm_mn<EPI, LDS, WM><<<grid, 256, smem, st>>>(ga, ea, mn_xcd_order(LDS, tasks, ga.S));
+    k_gemm_lds<EPI, WM><<<dim3((tasks + 7) / 8 * 8), 256, ring, st>>>(ga, ea, tasks > 512 ? 1 : 0);
     return hipGetLastError();
 }
 
 template <int EPI>
-static hipError_t launch_mn(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
-    const int wm = mn_wave_mtiles(EPI, ga.N, ga.K, ga.M);
-    if (mn_lds(EPI, ga.N, ga.K, ga.M))
-        return wm == 1 ? launch_mn_wm<EPI, true, 1>(ga, ea, st) : launch_mn_wm<EPI, true, 2>(ga, ea, st);
-    if (wm == 1) return launch_mn_wm<EPI, false, 1>(ga, ea, st);
-    return launch_mn_wm<EPI, false, 2>(ga, ea, st);
+static hipError_t launch_lds(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
+    return lds_wave_mtiles(ga.M) == 1 ? launch_lds_wm<EPI, 1>(ga, ea, st) : launch_lds_wm<EPI, 2>(ga, ea, st);
+}
+
+template <int EPI, int WM, int WN>
+static hipError_t launch_tile_shape(const GemmArgs& ga, const EpiArgs& ea, const TileShape& ts, hipStream_t st) {
+    constexpr int lds = 4 * WM * tile_exchange_stripes(WM, WN) * 1024 * 4;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tile<EPI, WM, WN>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const dim3 grid((ts.gx * ts.gy * ts.S + 7) / 8 * 8);
+    k_gemm_tile<EPI, WM, WN><<<grid, 256, lds, st>>>(ga, ea, ts);
+    return hipGetLastError();
+}
+
+template <int EPI>
+static hipError_t launch_tile(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
+    const TileShape ts = tile_shape(ga.N, ga.K, ga.M, EPI);
+    if (ts.S != ga.S) return hipErrorInvalidValue;
+    if constexpr (EPI == EPI_PARTIAL) {
+        if (ts.WN == 2)
+            return ts.WM == 3 ? launch_tile_shape<EPI, 3, 2>(ga, ea, ts, st) : launch_tile_shape<EPI, 4, 2>(ga, ea, ts, st);
+    }
+    if (ts.WM == 3)
+        return ts.WN == 3 ? launch_tile_shape<EPI, 3, 3>(ga, ea, ts, st) : launch_tile_shape<EPI, 3, 4>(ga, ea, ts, st);
+    if (ts.WM == 4 && ts.WN == 3) return launch_tile_shape<EPI, 4, 3>(ga, ea, ts, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, GemmShape g, float* part,
@@ -882,16 +906,17 @@ hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, Ge
     if (M <= 0) return hipSuccess;
     if (g.K % 16 || g.N % 32 || g.S < 1) return hipErrorInvalidValue;
     GemmArgs ga{X, Wp, M, g.N, g.K, g.S, g.KW, part, dn};
-    if (M > kMaxRows) {  // prefill chunks: the compute-bound tile kernel (shape from gemm_shape_mn)
-        if (M > kMaxPrefillRows || g.NS != 4 || dn) return hipErrorInvalidValue;
+    if (g.NS == kTileShapes) {  // shape from gemm_shape_mn
+        if (M > kMaxPrefillRows || dn) return hipErrorInvalidValue;
         switch (epi) {
-            case EPI_QKV: return launch_mn<EPI_QKV>(ga, ea, st);
-            case EPI_SWIGLU: return launch_mn<EPI_SWIGLU>(ga, ea, st);
-            case EPI_PARTIAL: return launch_mn<EPI_PARTIAL>(ga, ea, st);
-            default: return launch_mn<EPI_STORE>(ga, ea, st);
+            case EPI_QKV: return launch_tile<EPI_QKV>(ga, ea, st);
+            case EPI_SWIGLU: return launch_lds<EPI_SWIGLU>(ga, ea, st);
+            case EPI_PARTIAL: return launch_tile<EPI_PARTIAL>(ga, ea, st);
+            default:
+                return lds_tiles(epi, g.N) ? launch_lds<EPI_STORE>(ga, ea, st) : launch_tile<EPI_STORE>(ga, ea, st);
         }
     }
-    if (g.KW < 1 || g.KW > kMaxKw || (g.NS != 1 && g.NS != 2)) return hipErrorInvalidValue;
+    if (M > kMaxRows || g.KW < 1 || g.KW > kMaxKw || (g.NS != 1 && g.NS != 2)) return hipErrorInvalidValue;
     if (epi == EPI_QKV && g.KW < 4) return hipErrorInvalidValue;  // epilogue staging: >= 256 threads
     switch (epi) {
         case EPI_QKV: return launch_epi<EPI_QKV>(ga, ea, g.NS, st);

@@ -1,0 +1,24 @@
+"""GPU: the prefill's tile GEMMs at their edges, through whole chunks against the
+oracle (tolerances of the prefill tests): row counts around the 3- and 4-tile row
+groups and the thresholds where a projection changes kernel (65, 129, 257 rows),
+stripe counts that 2, 3 and 4 do not divide, K ranges that leave waves without a
+step, with a partial group and with several load groups."""
+import pytest
+
+import cdbgen
+from test_gpu_prefill import HD96, ODD, run_prefill
+
+pytestmark = pytest.mark.gpu
+
+# 74 k steps in the down projection: 18 or 19 per wave, two load groups of 8 and a remainder
+LONG = cdbgen.shrink(cdbgen.TINY, name="tiny-74", d_ff=1184, r_max=2)
+
+
+@pytest.mark.parametrize("rows", [64, 65, 97, 128, 129, 161, 256, 257, 289, 512])
+@pytest.mark.parametrize("shape", [ODD, HD96, LONG], ids=lambda s: s.name)
+def test_chunk_rows(shape, rows):
+    w = cdbgen.model_weights(shape)
+    prompt = cdbgen.prompt_ids(shape.vocab, 1, rows, seed=90)[0]
+    print(f"[gpu] tile GEMM {shape.name}: {rows} rows", flush=True)
+    err = run_prefill(shape, w, prompt, [rows])
+    print(f"[gpu]   {err}", flush=True)
