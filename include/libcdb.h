@@ -236,13 +236,13 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
 
 /* cdb_loop_step for callers that cannot allocate memory (code under HIP graph
  * capture, serving loops and harnesses that forbid allocation): the same
- * computation and outputs, with its scratch taken from a 66 MiB array the
+ * computation and outputs, with its scratch taken from a 84 MiB array the
  * library keeps in device memory (one per GPU, held until the process ends)
  * instead of a workspace argument.  It allocates and frees nothing.
  *   d_error: device int32, required; receives the sticky device error codes
  *   (CDB_DEV_*) that cdb_loop_step keeps in its workspace.  The caller zeroes
  *   it once and reads (and re-zeroes) it outside the hot path.
- * Calls whose workspace without the attention's split scratch would exceed
+ * Calls whose workspace without what only speeds them up would exceed
  * 48 MiB (e.g. more than 256 rows of the Ouro-shaped model) return
  * CDB_ERR_CAPACITY before anything is enqueued.  Nothing carries over between
  * calls in the scratch.  Every call on one GPU shares its scratch: calls that

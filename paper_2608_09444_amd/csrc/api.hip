@@ -111,7 +111,10 @@ WsLayout ws_layout(const cdb_model_desc& d, int rows, bool prefill) {
     off = align256(off + 3 * M * 4);
     L.lm = off;  // prefill without logits: the LM head of the last 32-row tile
     off = align256(off + (size_t)32 * d.vocab * 4);
-    L.base = off;
+    // (which calls are accepted does not follow the splits of the day)
+    const size_t ref = (size_t)std::max({gemm_reference_splits(d.d, d.d), gemm_reference_splits(d.d, d.d_ff),
+                                         d.injection ? gemm_reference_splits(d.d, 2 * d.d) : 0}) * D;
+    L.base = off - align256(part * M * 4) + align256(ref * M * 4);
     // segment records and arrival counters of the split attention, for as many
     // rows as it takes (also in larger workspaces, which serve smaller calls)
     const size_t split = std::min(rows, (kAttnSplitItems - 1) / d.n_heads);
@@ -434,9 +437,10 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
 // looked up once per device.
 // Calls are accepted up to kNoAllocLimit bytes of the regions every call needs;
 // the split attention's come on top, at most 511 (row, head) pairs' records and
-// counters (17 MB).
+// counters (17 MB), and split partials beyond the reference splits', at most 256
+// rows of 16384 values (splits x d, see gemm_shape).
 constexpr size_t kNoAllocLimit = (size_t)48 << 20;
-constexpr size_t kNoAllocScratchBytes = kNoAllocLimit + ((size_t)18 << 20);
+constexpr size_t kNoAllocScratchBytes = kNoAllocLimit + ((size_t)36 << 20);
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {

@@ -103,6 +103,7 @@ struct GemmShape {
     int NS;           // 32-column stripes per workgroup (1 or 2), or kTileShapes: the tile kernels
 };
 constexpr int kTileShapes = 4;
+constexpr int kTileFixed = 5;  // or: the register tile kernel at the given splits
 
 // ---------------------------------------------------------------- layouts
 struct WeightLayout {
@@ -120,6 +121,7 @@ struct WsLayout {
 WsLayout ws_layout(const cdb_model_desc& d, int rows, bool prefill);  // of a stage call, or of cdb_prefill
 
 GemmShape gemm_shape(int N, int K, int epi, int M);  // M <= kMaxRows
+int gemm_reference_splits(int N, int K);
 GemmShape gemm_shape_mn(int N, int K, int M, int epi);  // tile kernels
 bool desc_supported(const cdb_model_desc& d);
 

@@ -10,9 +10,8 @@
 //    weight byte compared with a 16-wide one.
 //  * A workgroup owns NS (1 or 2) 32-column stripes and one K split; its KW
 //    waves split that K range further.  Each wave streams its weight tiles and the matching
-//    activation fragments (L2-resident) in batches, double-buffered in
-//    registers so one batch is in flight while the previous one feeds the
-//    MFMAs.  The KW partial tiles are summed in LDS in wave order.
+//    activation fragments (L2-resident), several k steps ahead in registers.
+//    The KW partial tiles are summed in LDS in wave order.
 //  * No reduction crosses workgroups inside the kernel.  Stripes whose K is
 //    split over S workgroups write fp32 partial tiles; the row kernel that
 //    runs next (residual add + RMSNorm) adds them in split order.  Every
@@ -45,6 +44,10 @@ struct QkvStage {
     const int* tok;      // [rows]
 };
 
+// The two halves of a rotated pair, rounded alike wherever they are computed.
+__device__ __forceinline__ float rope_first(float xf, float xs, float c, float s) { return fmaf(xf, c, -(xs * s)); }
+__device__ __forceinline__ float rope_second(float xf, float xs, float c, float s) { return fmaf(xs, c, xf * s); }
+
 // split: the workgroup's K split (EPI_PARTIAL writes partial tile `split`)
 template <int EPI>
 __device__ __forceinline__ void epilogue_elem(float val, float partner, int m, int p, int split, const GemmArgs& ga,
@@ -69,7 +72,7 @@ __device__ __forceinline__ void epilogue_elem(float val, float partner, int m, i
         if (part < 2) {
             const float2 cs = qs.rope ? qs.rope[m * 16 + jj] : ea.rope[(size_t)m * (ea.hd >> 1) + gi * 16 + jj];
             const float xf = half ? partner : val, xs = half ? val : partner;
-            outv = half ? (xs * cs.x + xf * cs.y) : (xf * cs.x - xs * cs.y);
+            outv = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
         }
         if (part == 0) {
             ea.q[(size_t)m * (ea.H * ea.hd) + head * ea.hd + dim] = outv;
@@ -151,7 +154,7 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
                     const float val = fs[(half * 16 + jj) * fld + m], partner = fs[((half ^ 1) * 16 + jj) * fld + m];
                     const float2 cs = srope ? srope[m * 16 + jj] : ea.rope[(size_t)m * half_hd + gi * 16 + jj];
                     const float xf = half ? partner : val, xs = half ? val : partner;
-                    o[i] = half ? (xs * cs.x + xf * cs.y) : (xf * cs.x - xs * cs.y);
+                    o[i] = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
                 }
                 float* dst = ea.q + (size_t)m * (ea.H * ea.hd) + head * ea.hd + gi * 16 + j4 + half * half_hd;
                 *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
@@ -177,7 +180,7 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
                             const float2 cs =
                                 srope ? srope[m * 16 + jj] : ea.rope[(size_t)m * half_hd + gi * 16 + jj];
                             const float xf = half ? partner : val, xs = half ? val : partner;
-                            outv = half ? (xs * cs.x + xf * cs.y) : (xf * cs.x - xs * cs.y);
+                            outv = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
                         }
                         o2[b] = outv;
                     }
@@ -193,10 +196,22 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
     }
 }
 
-// k steps per register load batch of the decode kernel (register budget: two
-// batches of NS weight + MT activation operands)
-__host__ __device__ constexpr int decode_batch_steps(int MT, int NS) {
-    return NS == 1 ? (MT <= 2 ? 8 : (MT == 4 ? 4 : 1)) : (MT <= 2 ? 4 : (MT == 4 ? 2 : 1));
+// A buffer resource over [p, p + bytes): operand tiles are loaded with one lane
+// offset register for all of them and the tile's offset in a scalar, where
+// 64-bit lane addresses would take registers from the k steps in flight.  The
+// arguments are wave-uniform.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(uint32_t)bytes, 0x00027000);
+}
+__device__ __forceinline__ u32x4 load_tile(__amdgpu_buffer_rsrc_t r, int lane_bytes, int tile_bytes) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes, tile_bytes, 0));
+}
+
+// k steps of one wave in flight in the decode kernel: as many as leave room
+// for NS x MT accumulator tiles in the 256 registers of a wave
+__host__ __device__ constexpr int decode_depth(int MT, int NS) {
+    const int d = (224 - 16 * MT * NS) / (4 * (MT + NS));
+    return d > 16 ? 16 : d;
 }
 
 // 32x32 tiles the decode kernel's wave reduction sums per round: all NS x MT
@@ -208,9 +223,8 @@ __host__ __device__ constexpr int decode_red_tiles(bool qkv, int MT, int NS) {
 }
 
 // MT = 32-row tiles of M covered by one pass (M <= 32 * MT); NS = adjacent
-// 32-column stripes per workgroup (they share every activation load); TAIL:
-// some wave's K range is not a whole number of load batches (decode_batch_steps).
-template <int EPI, int MT, int NS, bool TAIL>
+// 32-column stripes per workgroup (they share every activation load).
+template <int EPI, int MT, int NS>
 __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     extern __shared__ __align__(16) float smem[];
     // the wave index as a scalar, so each wave's K range and its batch tests
@@ -236,49 +250,41 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     // a workgroup's last stripes may lie past the matrix (an odd stripe count
     // with NS = 2): they re-read the last stripe and their results are not stored
     const int stripes = ga.N >> 5;
-    const u32x4* wsrc[NS];
+    const int ns0 = min(nt, stripes - 1);
+    const __amdgpu_buffer_rsrc_t wr = tile_rsrc(reinterpret_cast<const u32x4*>(ga.Wp) + (size_t)ns0 * KS * 64,
+                                                (size_t)min(NS, stripes - ns0) * KS * 1024);
+    int wofs[NS];
 #pragma unroll
-    for (int ns = 0; ns < NS; ++ns)
-        wsrc[ns] = reinterpret_cast<const u32x4*>(ga.Wp) + (size_t)min(nt + ns, stripes - 1) * KS * 64 + lane;
+    for (int ns = 0; ns < NS; ++ns) wofs[ns] = (min(nt + ns, stripes - 1) - ns0) * KS * 1024;
     // X is in fragment layout: the operand of m-tile t at k step k is the 1 KiB tile (t, k)
-    const u32x4* xsrc = reinterpret_cast<const u32x4*>(ga.X) + lane;
-    constexpr int CH = decode_batch_steps(MT, NS);
-
-    // Two register sets: the next batch's loads are in flight while the
-    // current batch feeds the MFMAs.
-    u32x4 wa[CH][NS], wb[CH][NS];
-    u32x4 xa[CH][MT], xb[CH][MT];
-    // Loads are unconditional (steps past the wave's range re-read its last
-    // step) so that the compiler keeps each batch's loads in flight across the
-    // other batch's MFMAs.  With TAIL, the wave's last batch skips the MFMAs of
-    // the steps past its range (a wave-uniform branch); without it every batch
-    // is whole and no step is tested.
-    auto load = [&](u32x4 (&w)[CH][NS], u32x4 (&x)[CH][MT], int c0) {
+    const __amdgpu_buffer_rsrc_t xr = tile_rsrc(ga.X, (size_t)MT * KS * 1024);
+    const int lofs = lane * 16;
+    // D k steps in flight; a slot is loaded again as soon as its MFMAs are issued
+    constexpr int D = decode_depth(MT, NS);
+    u32x4 w[D][NS], x[D][MT];
+    auto load = [&](int i, int ks) {
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int ks = min(c0 + i, ks1 - 1);
+        for (int ns = 0; ns < NS; ++ns) w[i][ns] = load_tile(wr, lofs, wofs[ns] + ks * 1024);
 #pragma unroll
-            for (int ns = 0; ns < NS; ++ns) w[i][ns] = wsrc[ns][(size_t)ks * 64];
-#pragma unroll
-            for (int t = 0; t < MT; ++t) x[i][t] = xsrc[((size_t)t * KS + ks) * 64];
-        }
+        for (int t = 0; t < MT; ++t) x[i][t] = load_tile(xr, lofs, (t * KS + ks) * 1024);
     };
-    auto step = [&](const u32x4 (&w)[NS], const u32x4 (&x)[MT]) {
+    auto mma = [&](int i) {
 #pragma unroll
-        for (int ns = 0; ns < NS; ++ns) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, w[ns]);
+        for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
             for (int t = 0; t < MT; ++t)
-                acc[ns][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, x[t]), acc[ns][t],
-                                                                     0, 0, 0);
-        }
+                acc[ns][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[i][ns]),
+                                                                     __builtin_bit_cast(bf16x8, x[i][t]), acc[ns][t], 0, 0, 0);
     };
-    auto compute = [&](const u32x4 (&w)[CH][NS], const u32x4 (&x)[CH][MT], int c0) {
+    const int n = ks1 - ks0, groups = n / D, rem = n - groups * D;
+    if (groups > 0) {
 #pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (!TAIL || c0 + i < ks1) step(w[i], x[i]);
-    };
-    if (ks0 < ks1) load(wa, xa, ks0);
+        for (int i = 0; i < D; ++i) load(i, ks0 + i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < D - 1; ++i)
+            if (i < rem) load(i, ks0 + i);
+    }
 
     // q/k/v epilogue inputs, loaded while the weight stream is in flight (no
     // wait on them before the main loop ends); above 64 rows the RoPE factors
@@ -308,12 +314,25 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
         }
     }
 
-    for (int c0 = ks0; c0 < ks1; c0 += 2 * CH) {
-        if (c0 + CH < ks1) load(wb, xb, c0 + CH);
-        compute(wa, xa, c0);
-        if (c0 + 2 * CH < ks1) load(wa, xa, c0 + 2 * CH);
-        if (c0 + CH < ks1) compute(wb, xb, c0 + CH);
+    if (groups > 0) {
+        int ks = ks0 + D;
+        for (int g = 1; g < groups; ++g, ks += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                mma(i);
+                load(i, ks + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            mma(i);
+            if (i < rem) load(i, ks + i);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < D - 1; ++i)
+        if (i < rem) mma(i);
 
     // Sum the KW wave tiles in wave order: with 8 waves (a grid of one
     // workgroup per CU at most) all NS x MT 32x32 tiles in one round where they
@@ -429,7 +448,7 @@ struct TileShape {
 __host__ __device__ constexpr int tile_depth(int WM, int WN) { return 200 / (4 * (WM + WN)) < 8 ? 200 / (4 * (WM + WN)) : 8; }
 
 template <int EPI, int WM, int WN>
-__device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, int nt0, int split, int lane,
+__device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, int live, int nt0, int split, int lane,
                                               const GemmArgs& ga, const EpiArgs& ea) {
     const int stripes = ga.N >> 5, half = lane >> 5;
     if (EPI == EPI_QKV) {
@@ -448,7 +467,7 @@ __device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, 
                 cs[a][2 * u + 1] = *reinterpret_cast<const float4*>(r + u * 8 + 2);
             }
         }
-        if (m >= ga.M) return;
+        if (m >= live) return;
 #pragma unroll
         for (int a = 0; a < WN; ++a) {
             const int g = nt0 + a;
@@ -463,8 +482,8 @@ __device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float xf = acc[a][u * 4 + i], xs = acc[a][8 + u * 4 + i];
-                    lo[i] = part < 2 ? xf * c[2 * i] - xs * c[2 * i + 1] : xf;
-                    hi[i] = part < 2 ? xs * c[2 * i] + xf * c[2 * i + 1] : xs;
+                    lo[i] = part < 2 ? rope_first(xf, xs, c[2 * i], c[2 * i + 1]) : xf;
+                    hi[i] = part < 2 ? rope_second(xf, xs, c[2 * i], c[2 * i + 1]) : xs;
                 }
                 const int dim = gi * 16 + u * 8 + half * 4;
                 if (part == 0) {
@@ -481,7 +500,7 @@ __device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, 
         }
         return;
     }
-    if (m >= ga.M) return;
+    if (m >= live) return;
 #pragma unroll
     for (int a = 0; a < WN; ++a) {
         if (nt0 + a >= stripes) break;
@@ -628,7 +647,7 @@ __global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, Tile
                 }
         }
     }
-    if (wave < WM) tile_epilogue<EPI, WM, WN>(sum, (mt0 + wave) * 32 + (lane & 31), nt0, s, lane, ga, ea);
+    if (wave < WM) tile_epilogue<EPI, WM, WN>(sum, (mt0 + wave) * 32 + (lane & 31), live_rows(ga.dn, ga.M), nt0, s, lane, ga, ea);
 }
 
 // Tile GEMM staged through LDS, for gate/up and full-width LM heads above 256
@@ -731,7 +750,7 @@ __global__ __launch_bounds__(256) void k_gemm_lds(GemmArgs ga, EpiArgs ea, int x
     }
 #pragma unroll
     for (int b = 0; b < WM; ++b)
-        tile_epilogue<EPI, WM, 2>(acc[b], (mt0 + b) * 32 + (lane & 31), nt0, 0, lane, ga, ea);
+        tile_epilogue<EPI, WM, 2>(acc[b], (mt0 + b) * 32 + (lane & 31), ga.M, nt0, 0, lane, ga, ea);
 }
 
 // Which projections above 256 rows take the LDS-staged kernel (see there).
@@ -745,14 +764,14 @@ static int lds_wave_mtiles(int M) { return ((M + 63) / 64) % 2 ? 1 : 2; }
 // pads fewer; 2 (split-K epilogue only), 3 or 4 stripes and the K splits by the
 // rounds that the grid takes on the 256 CUs (a workgroup fills one), each
 // costing its k steps per wave and a fixed part (in KiB of operands), plus the
-// split partials' trip through memory.
-static TileShape tile_shape(int N, int K, int M, int epi) {
+// split partials' trip through memory.  fixed_S: the splits are given.
+static TileShape tile_shape(int N, int K, int M, int epi, int fixed_S = 0) {
     const int mt = (M + 31) / 32, gy = (mt + 3) / 4, WM = (mt + gy - 1) / gy, stripes = N / 32, KS = K / 16;
     TileShape best{};
     double cost = 1e30;
     for (int WN = epi == EPI_PARTIAL ? 2 : 3; WN <= (WM == 4 ? 3 : 4); ++WN)  // (4 x 4 tiles exceed the register file)
         for (int S = 1; S <= (epi == EPI_PARTIAL ? 8 : 1); ++S) {
-            if (S > 1 && KS / S < 32) break;
+            if (fixed_S ? S != fixed_S : S > 1 && KS / S < 32) continue;
             const int gx = (stripes + WN - 1) / WN, rounds = (gx * gy * S + 255) / 256;
             const double steps = (double)((KS + S - 1) / S + 3) / 4;
             const double c = rounds * (steps * (WM + WN) + 100) + 70.0 * (S - 1) * ((double)M * N / (1 << 20));
@@ -782,45 +801,48 @@ GemmShape gemm_shape(int N, int K, int epi, int M) {
     if (epi == EPI_PARTIAL) {
         while (stripes * S < 256 && KS / (S * 2) >= 64) S *= 2;
     }
-    // Two stripes per workgroup share every activation load.  Wide projections
-    // without a K split (gate/up, LM head) take them at up to 128 rows (a
-    // 256-row pass holds one stripe); split-K projections over long K ranges
-    // (and q/k/v, whose epilogue handles a pair) take them at 65-128 rows, where
-    // each weight byte brings 4 activation bytes from L2 and that stream bounds
-    // the kernel: with at least 160 k steps per workgroup (Huginn-shaped O,
-    // down and q/k/v: 36 -> 28, 99 -> 69 and 75 -> 54 us), not with 128 or fewer
-    // (Ouro-shaped q/k/v: 15 -> 22 us), nor below 65 rows.
+    // Wide projections without a K split (gate/up, LM head): two stripes per
+    // workgroup share every activation load at up to 128 rows (a 256-row pass
+    // holds one stripe).
     const bool pair_wide = epi != EPI_QKV && epi != EPI_PARTIAL && S == 1 && stripes > 256 && stripes % 2 == 0 &&
                            KS >= 64;
-    const bool pair_long = (epi == EPI_PARTIAL || epi == EPI_QKV) && KS / S >= 160;
-    const int NS = (pair_wide && MT < 8) || (pair_long && MT == 4) ? 2 : 1;
+    // Long K ranges (Huginn widths): 4 waves per workgroup at every row count,
+    // which lets the tile kernel serve more than 64 rows with the same sums
+    // (there each weight byte brings 4 activation bytes, and the skinny kernel
+    // reads the activations once per one or two stripes: at 128 rows q/k/v 54,
+    // gate/up 123, down 70, O 27 us).  Split so that pairs of stripes fill the
+    // chip once in the tile kernel; in the skinny kernel two such workgroups
+    // share a CU.
+    if (KS / S >= 160) {
+        int T = 1;
+        if (epi == EPI_PARTIAL) {
+            T = 256 / ((stripes + 1) / 2);
+            T = T < 1 ? 1 : (T > 8 ? 8 : T);
+            while (T > 1 && KS / T < 64) --T;
+        }
+        return GemmShape{N, K, T, 4, M > 64 ? kTileFixed : (pair_wide ? 2 : 1)};
+    }
+    const int NS = pair_wide && MT < 8 ? 2 : 1;
     // waves per workgroup: 8 (more weight bytes in flight per CU) while the
     // grid fits the chip in one round, counted with the stripe pairs where
     // they may be used, else 4
-    const int groups = (pair_wide || pair_long) ? (stripes + 1) / 2 : stripes;
+    const int groups = pair_wide ? (stripes + 1) / 2 : stripes;
     const int KW = groups * S <= 256 && KS / S >= 32 ? 8 : 4;
     return GemmShape{N, K, S, KW, NS};
 }
 
-// Whether some wave's K range in k_gemm (the same proportional split of each
-// workgroup's split over its KW waves) is not a whole number of batches.
-static bool decode_has_tail(int K, int S, int KW, int ch) {
-    const int KS = K / 16;
-    for (int s = 0; s < S; ++s) {
-        const int a0 = (int)(((long)s * KS) / S), a1 = (int)(((long)(s + 1) * KS) / S);
-        for (int w = 0; w < KW; ++w) {
-            const int n = (int)(((long)(w + 1) * (a1 - a0)) / KW) - (int)(((long)w * (a1 - a0)) / KW);
-            if (n % ch) return true;
-        }
-    }
-    return false;
+// The K splits a call's accepted size is reckoned with (see ws_layout).
+int gemm_reference_splits(int N, int K) {
+    int S = 1;
+    while (N / 32 * S < 256 && K / 16 / (S * 2) >= 64) S *= 2;
+    return S;
 }
 
-template <int EPI, int MT, int NS, bool TAIL>
-static hipError_t launch_tail(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
+template <int EPI, int MT, int NS>
+static hipError_t launch_mt(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<EPI, MT, NS, TAIL>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<EPI, MT, NS>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -829,14 +851,8 @@ static hipError_t launch_tail(const GemmArgs& ga, const EpiArgs& ea, hipStream_t
     size_t lds = ((size_t)ga.KW * (rt > 1 && ga.KW == 8 ? rt : 1) * 1024 + (size_t)NS * 32 * (MT * 32 + 1)) * 4;
     if (EPI == EPI_QKV) lds += (size_t)NS * MT * 32 * 16 * 8 + (size_t)MT * 32 * 2 * 4;
     dim3 grid((ga.N / 32 + NS - 1) / NS, ga.S);
-    k_gemm<EPI, MT, NS, TAIL><<<grid, ga.KW * 64, lds, st>>>(ga, ea);
+    k_gemm<EPI, MT, NS><<<grid, ga.KW * 64, lds, st>>>(ga, ea);
     return hipGetLastError();
-}
-
-template <int EPI, int MT, int NS>
-static hipError_t launch_mt(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
-    return decode_has_tail(ga.K, ga.S, ga.KW, decode_batch_steps(MT, NS)) ? launch_tail<EPI, MT, NS, true>(ga, ea, st)
-                                                                          : launch_tail<EPI, MT, NS, false>(ga, ea, st);
 }
 
 template <int EPI, int NS>
@@ -889,7 +905,7 @@ static hipError_t launch_tile_shape(const GemmArgs& ga, const EpiArgs& ea, const
 
 template <int EPI>
 static hipError_t launch_tile(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
-    const TileShape ts = tile_shape(ga.N, ga.K, ga.M, EPI);
+    const TileShape ts = tile_shape(ga.N, ga.K, ga.M, EPI, ga.S);
     if (ts.S != ga.S) return hipErrorInvalidValue;
     if constexpr (EPI == EPI_PARTIAL) {
         if (ts.WN == 2)
@@ -914,6 +930,14 @@ hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, Ge
             case EPI_PARTIAL: return launch_tile<EPI_PARTIAL>(ga, ea, st);
             default:
                 return lds_tiles(epi, g.N) ? launch_lds<EPI_STORE>(ga, ea, st) : launch_tile<EPI_STORE>(ga, ea, st);
+        }
+    }
+    if (g.NS == kTileFixed) {
+        switch (epi) {
+            case EPI_QKV: return launch_tile<EPI_QKV>(ga, ea, st);
+            case EPI_SWIGLU: return launch_tile<EPI_SWIGLU>(ga, ea, st);
+            case EPI_PARTIAL: return launch_tile<EPI_PARTIAL>(ga, ea, st);
+            default: return launch_tile<EPI_STORE>(ga, ea, st);
         }
     }
     if (M > kMaxRows || g.KW < 1 || g.KW > kMaxKw || (g.NS != 1 && g.NS != 2)) return hipErrorInvalidValue;
