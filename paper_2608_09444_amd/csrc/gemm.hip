@@ -1,5 +1,5 @@
 // Skinny bf16 GEMM for the block projections: Y[M][N] = X[M][K] . W[N][K]^T
-// with M = rows of one stage call (ragged, <= 256) and the weight streamed from
+// with M = rows of one stage call (ragged, <= 128) and the weight streamed from
 // HBM exactly once per call.
 //
 // Design (gfx950):
@@ -21,6 +21,8 @@
 //    16 first-half and the 16 matching second-half dims of one head), SwiGLU (a
 //    group is 16 gate and the 16 matching up columns), plain fp32 store, and
 //    the split-K partial store.
+#include <algorithm>
+
 #include "cdb_internal.h"
 
 namespace cdb {
@@ -534,7 +536,7 @@ __host__ __device__ constexpr int tile_exchange_stripes(int WM, int WN) {
     return 4 * WM * WN * 1024 * 4 <= 160 * 1024 ? WN : (WN + 1) / 2;
 }
 
-template <int EPI, int WM, int WN>
+template <int EPI, int WM, int WN, int PASSES>
 __global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, TileShape ts) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = ga.K >> 4, stripes = ga.N >> 5;
@@ -544,7 +546,6 @@ __global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, Tile
     if ((int)(blockIdx.x >> 3) >= per || t >= tasks) return;
     const int by = t % ts.gy, s = (t / ts.gy) % ts.S, bx = t / (ts.gy * ts.S);
     const int a0 = (int)(((long)s * KS) / ts.S), a1 = (int)(((long)(s + 1) * KS) / ts.S);
-    const int k0 = a0 + (wave * (a1 - a0)) / 4, k1 = a0 + ((wave + 1) * (a1 - a0)) / 4;
     const int nt0 = bx * WN, mt0 = by * WM;
 
     floatx16 acc[WM][WN];
@@ -580,71 +581,103 @@ __global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, Tile
                 acc[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[i][a]),
                                                                     __builtin_bit_cast(bf16x8, x[i][b]), acc[b][a], 0, 0, 0);
     };
-    // groups of D k steps: a slot's next load is issued as soon as its MFMAs are
-    const int n = k1 - k0, groups = n / D, rem = n - groups * D;
-    int ks = k0;
-    if (groups > 0) {
-#pragma unroll
-        for (int i = 0; i < D; ++i) load(i, ks + i);
-        for (int g = 1; g < groups; ++g, ks += D) {
-#pragma unroll
-            for (int i = 0; i < D; ++i) {
-                mma(i);
-                load(i, ks + D + i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            mma(i);
-            if (i < rem) load(i, ks + D + i);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-            if (i < rem) load(i, ks + i);
-    }
-#pragma unroll
-    for (int i = 0; i < D - 1; ++i)
-        if (i < rem) mma(i);
-
-    // exchange: wave v's copy of (m-tile b, stripe a), in lane order
+    // The K range is cut into 4 PASSES parts, as the skinny kernel cuts it over
+    // its waves: wave w takes part w and, of 8, then part w + 4; the parts are
+    // summed in order.  Groups of D k steps: a slot's next load is issued as soon
+    // as its MFMAs are.
+    auto part_begin = [&](int part) { return a0 + (part * (a1 - a0)) / (4 * PASSES); };
     extern __shared__ __align__(16) float smem[];
     constexpr int EX = tile_exchange_stripes(WM, WN);
     floatx16 sum[WN];
 #pragma unroll
-    for (int r = 0; r < WN; r += EX) {
-        if (r > 0) __syncthreads();  // the round before has been read
-        constexpr int NE = EX;
+    for (int a = 0; a < WN; ++a)
 #pragma unroll
-        for (int b = 0; b < WM; ++b)
+        for (int j = 0; j < 16; ++j) sum[a][j] = 0.f;
+    int ks = part_begin(wave), groups = (part_begin(wave + 1) - ks) / D, rem = part_begin(wave + 1) - ks - groups * D;
+    if (groups > 0) {
 #pragma unroll
-            for (int a = r; a < r + NE && a < WN; ++a) {
-                float4* dst = reinterpret_cast<float4*>(smem) + (size_t)((wave * WM + b) * NE + a - r) * 256 + lane;
+        for (int i = 0; i < D; ++i) load(i, ks + i);
+    } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    dst[u * 64] = make_float4(acc[b][a][u * 4], acc[b][a][u * 4 + 1], acc[b][a][u * 4 + 2], acc[b][a][u * 4 + 3]);
-            }
-        __syncthreads();
-        if (wave < WM) {
+        for (int i = 0; i < D - 1; ++i)
+            if (i < rem) load(i, ks + i);
+    }
 #pragma unroll
-            for (int a = r; a < r + NE && a < WN; ++a)
+    for (int pass = 0; pass < PASSES; ++pass) {
+        if (pass > 0) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int b = 0; b < WM; ++b)
 #pragma unroll
-                    for (int src = 0; src < 4; ++src) {
-                        const float4 p = reinterpret_cast<const float4*>(smem)[(size_t)((src * WM + wave) * NE + a - r) * 256 + u * 64 + lane];
-                        v.x += p.x;
-                        v.y += p.y;
-                        v.z += p.z;
-                        v.w += p.w;
-                    }
-                    sum[a][u * 4] = v.x;
-                    sum[a][u * 4 + 1] = v.y;
-                    sum[a][u * 4 + 2] = v.z;
-                    sum[a][u * 4 + 3] = v.w;
+                for (int a = 0; a < WN; ++a)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) acc[b][a][j] = 0.f;
+        }
+        if (groups > 0) {
+            for (int g = 1; g < groups; ++g, ks += D) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    mma(i);
+                    load(i, ks + D + i);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+            }
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                mma(i);
+                if (i < rem) load(i, ks + D + i);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < D - 1; ++i)
+            if (i < rem) mma(i);
+        // exchange: wave v's copy of (m-tile b, stripe a), in lane order
+#pragma unroll
+        for (int r = 0; r < WN; r += EX) {
+            if (r > 0 || pass > 0) __syncthreads();  // the round before has been read
+            constexpr int NE = EX;
+#pragma unroll
+            for (int b = 0; b < WM; ++b)
+#pragma unroll
+                for (int a = r; a < r + NE && a < WN; ++a) {
+                    float4* dst = reinterpret_cast<float4*>(smem) + (size_t)((wave * WM + b) * NE + a - r) * 256 + lane;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        dst[u * 64] = make_float4(acc[b][a][u * 4], acc[b][a][u * 4 + 1], acc[b][a][u * 4 + 2], acc[b][a][u * 4 + 3]);
+                }
+            __syncthreads();
+            if (wave < WM) {
+#pragma unroll
+                for (int a = r; a < r + NE && a < WN; ++a)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        float4 v = make_float4(sum[a][u * 4], sum[a][u * 4 + 1], sum[a][u * 4 + 2], sum[a][u * 4 + 3]);
+#pragma unroll
+                        for (int src = 0; src < 4; ++src) {
+                            const float4 p = reinterpret_cast<const float4*>(smem)[(size_t)((src * WM + wave) * NE + a - r) * 256 + u * 64 + lane];
+                            v.x += p.x;
+                            v.y += p.y;
+                            v.z += p.z;
+                            v.w += p.w;
+                        }
+                        sum[a][u * 4] = v.x;
+                        sum[a][u * 4 + 1] = v.y;
+                        sum[a][u * 4 + 2] = v.z;
+                        sum[a][u * 4 + 3] = v.w;
+                    }
+            }
+        }
+        if (pass + 1 < PASSES) {  // the second part's first loads (before the exchange they would exceed the registers)
+            ks = part_begin(wave + 4);
+            groups = (part_begin(wave + 5) - ks) / D;
+            rem = part_begin(wave + 5) - ks - groups * D;
+            if (groups > 0) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) load(i, ks + i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < D - 1; ++i)
+                    if (i < rem) load(i, ks + i);
+            }
         }
     }
     if (wave < WM) tile_epilogue<EPI, WM, WN>(sum, (mt0 + wave) * 32 + (lane & 31), live_rows(ga.dn, ga.M), nt0, s, lane, ga, ea);
@@ -764,12 +797,15 @@ static int lds_wave_mtiles(int M) { return ((M + 63) / 64) % 2 ? 1 : 2; }
 // pads fewer; 2 (split-K epilogue only), 3 or 4 stripes and the K splits by the
 // rounds that the grid takes on the 256 CUs (a workgroup fills one), each
 // costing its k steps per wave and a fixed part (in KiB of operands), plus the
-// split partials' trip through memory.  fixed_S: the splits are given.
-static TileShape tile_shape(int N, int K, int M, int epi, int fixed_S = 0) {
-    const int mt = (M + 31) / 32, gy = (mt + 3) / 4, WM = (mt + gy - 1) / gy, stripes = N / 32, KS = K / 16;
+// split partials' trip through memory.  fixed_S: the splits are given; two_parts:
+// the kernel whose waves run two parts of K each.
+static TileShape tile_shape(int N, int K, int M, int epi, int fixed_S = 0, bool two_parts = false) {
+    const int mt = (M + 31) / 32, stripes = N / 32, KS = K / 16;
+    // (the two-part kernel with q/k/v's epilogue spills at 4 m-tiles: 39 us against 24 at 200 Ouro-shaped rows)
+    const int most = two_parts && epi == EPI_QKV ? 3 : 4, gy = (mt + most - 1) / most, WM = std::max(3, (mt + gy - 1) / gy);
     TileShape best{};
     double cost = 1e30;
-    for (int WN = epi == EPI_PARTIAL ? 2 : 3; WN <= (WM == 4 ? 3 : 4); ++WN)  // (4 x 4 tiles exceed the register file)
+    for (int WN = epi == EPI_PARTIAL ? 2 : 3; WN <= (WM == 4 || two_parts ? 3 : 4); ++WN)  // (4 x 4 tiles exceed the register file)
         for (int S = 1; S <= (epi == EPI_PARTIAL ? 8 : 1); ++S) {
             if (fixed_S ? S != fixed_S : S > 1 && KS / S < 32) continue;
             const int gx = (stripes + WN - 1) / WN, rounds = (gx * gy * S + 255) / 256;
@@ -792,7 +828,6 @@ GemmShape gemm_shape(int N, int K, int epi, int M) {
     // workgroup) only regroups whole stripes, and follows the row count.
     const int stripes = N / 32;
     const int KS = K / 16;
-    const int MT = M <= 32 ? 1 : (M <= 64 ? 2 : (M <= 128 ? 4 : 8));  // 32-row tiles per pass
     // K split until the grid covers the chip, keeping at least 64 k steps per
     // workgroup (a 4-way split of a 2048-long K loses more to each workgroup's
     // fixed costs than its extra workgroups gain: Ouro's O at 64 rows 6.4 ->
@@ -802,17 +837,17 @@ GemmShape gemm_shape(int N, int K, int epi, int M) {
         while (stripes * S < 256 && KS / (S * 2) >= 64) S *= 2;
     }
     // Wide projections without a K split (gate/up, LM head): two stripes per
-    // workgroup share every activation load at up to 128 rows (a 256-row pass
-    // holds one stripe).
+    // workgroup share every activation load.
     const bool pair_wide = epi != EPI_QKV && epi != EPI_PARTIAL && S == 1 && stripes > 256 && stripes % 2 == 0 &&
                            KS >= 64;
     // Long K ranges (Huginn widths): 4 waves per workgroup at every row count,
-    // which lets the tile kernel serve more than 64 rows with the same sums
-    // (there each weight byte brings 4 activation bytes, and the skinny kernel
-    // reads the activations once per one or two stripes: at 128 rows q/k/v 54,
-    // gate/up 123, down 70, O 27 us).  Split so that pairs of stripes fill the
-    // chip once in the tile kernel; in the skinny kernel two such workgroups
-    // share a CU.
+    // which lets the tile kernel serve more than 64 rows with the same sums in
+    // one pass (there each weight byte brings 4 activation bytes, and the skinny
+    // kernel read the activations once per two stripes: at 128 rows gate/up
+    // 121 -> 104 us, O 27 -> 18, down 71 -> 52, q/k/v 53 -> 55).  Split so that pairs of
+    // stripes fill the chip once in the tile kernel (3 ways for 165 stripes); in
+    // the skinny kernel two such workgroups share a CU (9 rows, O, down and
+    // adapter together: 304 -> 246 us per step against 2 ways and 8 waves).
     if (KS / S >= 160) {
         int T = 1;
         if (epi == EPI_PARTIAL) {
@@ -822,13 +857,17 @@ GemmShape gemm_shape(int N, int K, int epi, int M) {
         }
         return GemmShape{N, K, T, 4, M > 64 ? kTileFixed : (pair_wide ? 2 : 1)};
     }
-    const int NS = pair_wide && MT < 8 ? 2 : 1;
+    const int NS = pair_wide ? 2 : 1;
     // waves per workgroup: 8 (more weight bytes in flight per CU) while the
     // grid fits the chip in one round, counted with the stripe pairs where
     // they may be used, else 4
     const int groups = pair_wide ? (stripes + 1) / 2 : stripes;
     const int KW = groups * S <= 256 && KS / S >= 32 ? 8 : 4;
-    return GemmShape{N, K, S, KW, NS};
+    // Above 128 rows a skinny workgroup would hold 8 tiles of accumulators and
+    // little in flight; the register tile kernel runs the same K parts (Ouro
+    // widths at 140 rows: q/k/v 27.4 -> 23.6 us, gate/up 46.1 -> 23.3, O and down
+    // 18.3 -> 13.4; at 100 rows the skinny kernel's 17.7 and 22.5 us are ahead).
+    return GemmShape{N, K, S, KW, M > 128 ? kTileFixed : NS};
 }
 
 // The K splits a call's accepted size is reckoned with (see ws_layout).
@@ -859,8 +898,7 @@ template <int EPI, int NS>
 static hipError_t launch_ns(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
     if (ga.M <= 32) return launch_mt<EPI, 1, NS>(ga, ea, st);
     if (ga.M <= 64) return launch_mt<EPI, 2, NS>(ga, ea, st);
-    if (ga.M <= 128) return launch_mt<EPI, 4, NS>(ga, ea, st);
-    return launch_mt<EPI, 8, 1>(ga, ea, st);  // two stripes of 256 rows exceed the register file
+    return launch_mt<EPI, 4, NS>(ga, ea, st);
 }
 
 template <int EPI>
@@ -888,24 +926,29 @@ static hipError_t launch_lds(const GemmArgs& ga, const EpiArgs& ea, hipStream_t 
     return lds_wave_mtiles(ga.M) == 1 ? launch_lds_wm<EPI, 1>(ga, ea, st) : launch_lds_wm<EPI, 2>(ga, ea, st);
 }
 
-template <int EPI, int WM, int WN>
-static hipError_t launch_tile_shape(const GemmArgs& ga, const EpiArgs& ea, const TileShape& ts, hipStream_t st) {
+template <int EPI, int WM, int WN, int PASSES>
+static hipError_t launch_tile_passes(const GemmArgs& ga, const EpiArgs& ea, const TileShape& ts, hipStream_t st) {
     constexpr int lds = 4 * WM * tile_exchange_stripes(WM, WN) * 1024 * 4;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tile<EPI, WM, WN>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tile<EPI, WM, WN, PASSES>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const dim3 grid((ts.gx * ts.gy * ts.S + 7) / 8 * 8);
-    k_gemm_tile<EPI, WM, WN><<<grid, 256, lds, st>>>(ga, ea, ts);
+    k_gemm_tile<EPI, WM, WN, PASSES><<<grid, 256, lds, st>>>(ga, ea, ts);
     return hipGetLastError();
+}
+
+template <int EPI, int WM, int WN>
+static hipError_t launch_tile_shape(const GemmArgs& ga, const EpiArgs& ea, const TileShape& ts, hipStream_t st) {
+    return ga.KW == 8 ? launch_tile_passes<EPI, WM, WN, 2>(ga, ea, ts, st) : launch_tile_passes<EPI, WM, WN, 1>(ga, ea, ts, st);
 }
 
 template <int EPI>
 static hipError_t launch_tile(const GemmArgs& ga, const EpiArgs& ea, hipStream_t st) {
-    const TileShape ts = tile_shape(ga.N, ga.K, ga.M, EPI, ga.S);
+    const TileShape ts = tile_shape(ga.N, ga.K, ga.M, EPI, ga.S, ga.KW == 8);
     if (ts.S != ga.S) return hipErrorInvalidValue;
     if constexpr (EPI == EPI_PARTIAL) {
         if (ts.WN == 2)
@@ -920,7 +963,7 @@ static hipError_t launch_tile(const GemmArgs& ga, const EpiArgs& ea, hipStream_t
 hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, GemmShape g, float* part,
                        const EpiArgs& ea, hipStream_t st, const int32_t* dn) {
     if (M <= 0) return hipSuccess;
-    if (g.K % 16 || g.N % 32 || g.S < 1) return hipErrorInvalidValue;
+    if (g.K % 16 || g.N % 32 || g.S < 1 || (g.KW != 4 && g.KW != 8)) return hipErrorInvalidValue;
     GemmArgs ga{X, Wp, M, g.N, g.K, g.S, g.KW, part, dn};
     if (g.NS == kTileShapes) {  // shape from gemm_shape_mn
         if (M > kMaxPrefillRows || dn) return hipErrorInvalidValue;
@@ -940,7 +983,7 @@ hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, Ge
             default: return launch_tile<EPI_STORE>(ga, ea, st);
         }
     }
-    if (M > kMaxRows || g.KW < 1 || g.KW > kMaxKw || (g.NS != 1 && g.NS != 2)) return hipErrorInvalidValue;
+    if (M > 128 || g.KW > kMaxKw || (g.NS != 1 && g.NS != 2)) return hipErrorInvalidValue;
     if (epi == EPI_QKV && g.KW < 4) return hipErrorInvalidValue;  // epilogue staging: >= 256 threads
     switch (epi) {
         case EPI_QKV: return launch_epi<EPI_QKV>(ga, ea, g.NS, st);
