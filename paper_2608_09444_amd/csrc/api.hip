@@ -436,8 +436,8 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
 // is a stand-in symbol); it uses the device address hipGetSymbolAddress gives,
 // looked up once per device.
 // Calls are accepted up to kNoAllocLimit bytes of the regions every call needs;
-// the split attention's come on top, at most 511 (row, head) pairs' records and
-// counters (17 MB), and split partials beyond the reference splits', at most 256
+// the split attention's come on top, at most 319 (row, head) pairs' records and
+// counters (11 MB), and split partials beyond the reference splits', at most 256
 // rows of 16384 values (splits x d, see gemm_shape).
 constexpr size_t kNoAllocLimit = (size_t)48 << 20;
 constexpr size_t kNoAllocScratchBytes = kNoAllocLimit + ((size_t)36 << 20);

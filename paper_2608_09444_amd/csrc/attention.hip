@@ -397,8 +397,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(const float* __restric
 //
 // With one workgroup per (head, pair) 6 rows at 3100 positions ran on 48 of 256
 // CUs: 130 us per layer; spread over segments 38 us (4.0 TB/s).  One row at 450
-// positions 13.6 -> 9.8 us, 23 rows at 400 positions 24.7 -> 24.3 us, 9 Huginn-
-// shaped rows (55 x 96 heads) 33 -> 28 us.
+// positions 13.6 -> 10.8 us.
 template <int HD>
 __global__ __launch_bounds__(kAttnWaves * 64) void k_attn_split(const float* __restrict__ q, KvTarget kv,
                                                                 const int32_t* __restrict__ seq,
@@ -515,10 +514,9 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn_split(const float* __r
     }
 }
 
-// Workgroups per (row, head) of the split form; 1: the paired form, which at
-// 512 (row, head) pairs has a workgroup for every CU (32 Ouro-shaped rows) and
-// needs no merge through memory.  Enough workgroups for four per CU, but no
-// more than a context the page table can hold has segments.
+// Workgroups per (row, head) of the split form; 1: the paired form.  Enough
+// workgroups for four per CU, but no more than a context the page table can hold
+// has segments.
 static int attn_splits(int M, int H, int max_pages) {
     if (M * H >= kAttnSplitItems) return 1;
     const int sp = attn_segment_pages(max_pages), nseg = (max_pages + sp - 1) / sp;

@@ -141,8 +141,11 @@ __host__ __device__ __forceinline__ int attn_segment_pages(int npg) {
     return p < 12 ? 12 : p;
 }
 // (row, head) pairs below which the decode attention spreads a row's segments
-// over several workgroups
-constexpr int kAttnSplitItems = 512;
+// over several workgroups.  One workgroup per row and head against several, 16
+// heads: 12 rows at 3100 positions 111 and 73 us, at 450 positions 21 and 19; 20
+// rows at 3100 positions (320 pairs) 117 and 116; 30 rows 128 and 168, 24 rows
+// at 450 positions 23 and 28; 9 rows of 55 heads 25 and 28.6.
+constexpr int kAttnSplitItems = 320;
 // Scratch of that form: segment records (attn_part_floats per row) and one
 // arrival counter per (row, head), zero between launches.
 struct AttnScratch {

@@ -39,7 +39,7 @@ def _rows(n, r_max):
 @pytest.mark.parametrize("hd,H", [(64, 4), (96, 3), (128, 2)])
 def test_segments_over_workgroups_give_the_same_bits(hd, H):
     s = _shape(hd, H)
-    n = 512 // H + (512 % H > 0)  # the smallest batch that keeps rows in one workgroup
+    n = 320 // H + (320 % H > 0)  # the smallest batch that keeps rows in one workgroup
     rows = _rows(n, s.r_max)
     print(f"[gpu] split attention {H} x {hd}: {n} rows vs their first {len(EDGES)}", flush=True)
     sys.stdout.flush()
