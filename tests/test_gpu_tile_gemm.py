@@ -6,6 +6,7 @@ step, with a partial group and with several load groups."""
 import pytest
 
 import cdbgen
+from test_gpu_edges import _batch_invariance
 from test_gpu_prefill import HD96, ODD, run_prefill
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +23,12 @@ def test_chunk_rows(shape, rows):
     print(f"[gpu] tile GEMM {shape.name}: {rows} rows", flush=True)
     err = run_prefill(shape, w, prompt, [rows])
     print(f"[gpu]   {err}", flush=True)
+
+
+@pytest.mark.parametrize("rows,alone", [(129, 64), (200, 128), (256, 33)])
+def test_loop_step_rows_keep_their_bits_above_128(rows, alone):
+    """The tile kernel's two-part passes against the skinny kernel's 8 waves, the same rows."""
+    s = cdbgen.shrink(cdbgen.OURO, name="ouro-1-layer", vocab=64, n_core=1)
+    r = cdbgen.decode_snapshot(rows, cdbgen.OURO_DEPTHS, s.r_max, 5, 60, stream=93)
+    print(f"[gpu] {rows} rows vs their first {alone}", flush=True)
+    _batch_invariance(s, cdbgen.model_weights(s), r, alone)
