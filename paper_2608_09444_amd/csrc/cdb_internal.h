@@ -104,6 +104,9 @@ struct GemmShape {
 };
 constexpr int kTileShapes = 4;
 constexpr int kTileFixed = 5;  // or: the register tile kernel at the given splits
+struct TileShape {
+    int WM, WN, gx, gy, S;  // m-tiles and stripes per workgroup, column and row groups, K splits
+};
 
 // ---------------------------------------------------------------- layouts
 struct WeightLayout {
@@ -123,6 +126,8 @@ WsLayout ws_layout(const cdb_model_desc& d, int rows, bool prefill);  // of a st
 GemmShape gemm_shape(int N, int K, int epi, int M);  // M <= kMaxRows
 int gemm_reference_splits(int N, int K);
 GemmShape gemm_shape_mn(int N, int K, int M, int epi);  // tile kernels
+// launch shape of the register tile kernel; fixed_S: the splits are given
+TileShape tile_shape(int N, int K, int M, int epi, int fixed_S = 0, bool two_parts = false);
 bool desc_supported(const cdb_model_desc& d);
 
 // ---------------------------------------------------------------- launchers

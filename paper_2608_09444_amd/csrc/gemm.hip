@@ -443,10 +443,6 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
 // Tile order: the dispatcher hands workgroup b to XCD b % 8, so each XCD takes
 // a contiguous range of tasks, row tile first: the row tiles that read one
 // weight tile run together on one XCD and share its L2.
-struct TileShape {
-    int WM, WN, gx, gy, S;  // m-tiles and stripes per workgroup, column and row groups, K splits
-};
-
 __host__ __device__ constexpr int tile_depth(int WM, int WN) { return 200 / (4 * (WM + WN)) < 8 ? 200 / (4 * (WM + WN)) : 8; }
 
 template <int EPI, int WM, int WN>
@@ -797,17 +793,18 @@ static int lds_wave_mtiles(int M) { return ((M + 63) / 64) % 2 ? 1 : 2; }
 // pads fewer; 2 (split-K epilogue only), 3 or 4 stripes and the K splits by the
 // rounds that the grid takes on the 256 CUs (a workgroup fills one), each
 // costing its k steps per wave and a fixed part (in KiB of operands), plus the
-// split partials' trip through memory.  fixed_S: the splits are given; two_parts:
-// the kernel whose waves run two parts of K each.
-static TileShape tile_shape(int N, int K, int M, int epi, int fixed_S = 0, bool two_parts = false) {
+// split partials' trip through memory.  fixed_S: the splits are given (gemm_shape's
+// may be more than the 8 that are tried here); two_parts: the kernel whose waves run
+// two parts of K each.
+TileShape tile_shape(int N, int K, int M, int epi, int fixed_S, bool two_parts) {
     const int mt = (M + 31) / 32, stripes = N / 32, KS = K / 16;
     // (the two-part kernel with q/k/v's epilogue spills at 4 m-tiles: 39 us against 24 at 200 Ouro-shaped rows)
     const int most = two_parts && epi == EPI_QKV ? 3 : 4, gy = (mt + most - 1) / most, WM = std::max(3, (mt + gy - 1) / gy);
     TileShape best{};
     double cost = 1e30;
     for (int WN = epi == EPI_PARTIAL ? 2 : 3; WN <= (WM == 4 || two_parts ? 3 : 4); ++WN)  // (4 x 4 tiles exceed the register file)
-        for (int S = 1; S <= (epi == EPI_PARTIAL ? 8 : 1); ++S) {
-            if (fixed_S ? S != fixed_S : S > 1 && KS / S < 32) continue;
+        for (int S = fixed_S ? fixed_S : 1; S <= (fixed_S ? fixed_S : epi == EPI_PARTIAL ? 8 : 1); ++S) {
+            if (!fixed_S && S > 1 && KS / S < 32) continue;
             const int gx = (stripes + WN - 1) / WN, rounds = (gx * gy * S + 255) / 256;
             const double steps = (double)((KS + S - 1) / S + 3) / 4;
             const double c = rounds * (steps * (WM + WN) + 100) + 70.0 * (S - 1) * ((double)M * N / (1 << 20));

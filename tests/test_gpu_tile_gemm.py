@@ -32,3 +32,13 @@ def test_loop_step_rows_keep_their_bits_above_128(rows, alone):
     r = cdbgen.decode_snapshot(rows, cdbgen.OURO_DEPTHS, s.r_max, 5, 60, stream=93)
     print(f"[gpu] {rows} rows vs their first {alone}", flush=True)
     _batch_invariance(s, cdbgen.model_weights(s), r, alone)
+
+
+@pytest.mark.parametrize("rows,alone", [(129, 64), (256, 128)])
+def test_many_splits_keep_their_bits_above_128(rows, alone):
+    """A long reduction onto few columns takes 16 splits (more than the tile kernel's own choice ever is)."""
+    s = cdbgen.shrink(cdbgen.TINY, name="512-16384", d=512, n_heads=8, d_ff=16384, vocab=64, n_prelude=0, n_core=1,
+                      n_coda=0)
+    r = cdbgen.decode_snapshot(rows, cdbgen.OURO_DEPTHS, s.r_max, 5, 60, stream=94)
+    print(f"[gpu] 16 splits: {rows} rows vs their first {alone}", flush=True)
+    _batch_invariance(s, cdbgen.model_weights(s), r, alone)
