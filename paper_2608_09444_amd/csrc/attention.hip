@@ -20,7 +20,9 @@
 // row-entry kernel, or by k_row_order for a standalone attention call) -- and
 // deals the pages of both to its 4 waves.  Each wave keeps one softmax state
 // per row.  With pairs, mixed and equal context lengths run at the same
-// bandwidth.
+// bandwidth.  More than kAttnPairs pairs (two workgroups per CU) leave some CUs
+// a workgroup more than others; then every row has a workgroup of its own,
+// longest first, and the short ones fill in.
 //
 // Order of the sums: a row's context is cut into segments (attn_segment_pages,
 // by its own page count); page p belongs to class p % 4; a class's pages of one
@@ -268,6 +270,17 @@ __device__ __forceinline__ void store_state(const SoftState<HD / 16>& st, int r,
     for (int e = 0; e < HD / 16; ++e) s_acc[r][wave][li * (HD / 16) + e] = st.acc[e];
 }
 
+// (row pair, head) workgroups above which a row has its own.  Pairs against rows
+// alone, 16 x 128 heads: 64 rows (512 pairs) at 640 positions 56 and 57 us, 66
+// rows (528) 71 and 62, 80 rows 75.6 and 73, 98 rows 94 and 87, 128 rows 108 and
+// 108, 160 rows 143 and 133; 55 x 96 heads at 510 positions: 18 rows (495) 33.4 and
+// 34.7, 28 rows (770) 55 and 48.5, 64 rows 112 and 106.  At 40 positions rows
+// alone cost up to 1.5 us (256 rows 20.7 and 22.2).  The live rows decide; the
+// grid is that of the capacity, whose empty workgroups cost a call of few live
+// rows 0.5 us (1 row of 128) to 1.4 us (of 256).
+constexpr int kAttnPairs = 512;
+__host__ __device__ __forceinline__ bool rows_alone(int n, int H) { return (n + 1) / 2 * H > kAttnPairs; }
+
 template <int HD>
 __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(const float* __restrict__ q, KvTarget kv,
                                                           const int32_t* __restrict__ seq,
@@ -285,11 +298,12 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(const float* __restric
     const float qscale = 1.4426950408889634f / sqrtf((float)HD);  // log2(e) / sqrt(hd)
     const size_t vofs = (size_t)H * kPage * HD;  // V follows K within a (layer, page)
 
-    // the pair: p-th longest and p-th shortest row (one row when they meet);
-    // with a device row count the grid covers the capacity M
+    // the pair: p-th longest and p-th shortest row (one row when they meet, or
+    // with rows alone); with a device row count the grid covers the capacity M
     const int n = live_rows(dn, M);
-    if (2 * pair >= n) return;
-    const int row0 = order[pair], row1 = (n - 1 - pair > pair) ? order[n - 1 - pair] : -1;
+    const bool alone = rows_alone(n, H);
+    if (alone ? pair >= n : 2 * pair >= n) return;
+    const int row0 = order[pair], row1 = (!alone && n - 1 - pair > pair) ? order[n - 1 - pair] : -1;
     const RowCtx rc0 = row_context(kv, seq, pos, row0);
     const RowCtx rc1 = row1 >= 0 ? row_context(kv, seq, pos, row1) : RowCtx{kv.page_table, 0, 0, false};
     if (tid == 0 && (!rc0.ok || (row1 >= 0 && !rc1.ok))) set_err(err, CDB_DEV_UNMAPPED_PAGE);
@@ -543,7 +557,7 @@ hipError_t launch_attention(const float* q, const KvTarget& kv, const int32_t* s
         }
         return hipGetLastError();
     }
-    dim3 grid(H, (M + 1) / 2);
+    dim3 grid(H, rows_alone(M, H) ? M : (M + 1) / 2);
     switch (hd) {
         case 64: k_attn<64><<<grid, kAttnWaves * 64, 0, st>>>(q, kv, seq, pos, order, M, H, out, err, dn); break;
         case 96: k_attn<96><<<grid, kAttnWaves * 64, 0, st>>>(q, kv, seq, pos, order, M, H, out, err, dn); break;

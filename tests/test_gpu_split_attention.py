@@ -75,3 +75,72 @@ def test_one_workgroup_form_against_fp32(hd, H):
         want = (pr[..., None] * v).sum(1).reshape(-1)
         err = (got[i] - want).abs()
         assert bool((err <= want.abs() * 2.0 ** -8 + 1e-4).all()), (p, float(err.max()))
+
+
+def _step_bits(s, rows_np, calls, unmap=None):
+    """Loop steps of the first `capacity` rows, `live` of them counted on the device (None: the host's count), one
+    after the other on one workspace from the same state and cache: [(states, scores, error code)].  unmap: a (row,
+    page) whose entry in the page table is -1."""
+    n = len(rows_np["pos"])
+    gm = cdb.DeviceModel(s, cdbgen.model_weights(s))
+    pt, max_pages, n_pages = _own_pages(s, rows_np)
+    if unmap is not None:
+        pt[unmap[0], int(rows_np["c"][unmap[0]]) + 1, unmap[1]] = -1
+    kv = cdb.PagedKV(s, n, max_pages, 0, n_pages, 0, fill="random")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(22)
+    kv.core.normal_(0.0, 1.0, generator=g)
+    kv.page_table.copy_(torch.from_numpy(pt))
+    state = cdb.State(s, n)
+    state.h.normal_(0.0, 1.0, generator=g)
+    h0 = state.h.clone()
+    ws = cdb.Workspace(gm.desc, n)
+    got = []
+    for capacity, live in calls:
+        print(f"[gpu]   {capacity} rows, {live} live", flush=True)
+        state.h.copy_(h0)
+        count = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
+        rows = cdb.Rows(*(rows_np[k][:capacity] for k in ("slot", "seq", "pos", "c", "depth")), d_n_rows=count)
+        out = cdb.StepOut(capacity)
+        cdb.cdb_loop_step(gm.model, kv.c, state.c, rows.c, out.c, ws.buf)
+        torch.cuda.synchronize()
+        got.append((state.h.clone(), out.score.clone(), cdb.cdb_read_device_error(ws.buf)))
+    return h0, got
+
+
+# 16 heads: a row's segments over several workgroups below 20 rows (4 workgroups at 19 rows, so each takes several
+# segments of the long rows), row pairs up to 64 rows (512 pairs), one workgroup per row above; the device count chooses
+# between the last two
+@pytest.mark.parametrize("hd", [64, 96, 128])
+def test_every_form_and_device_count_gives_the_same_bits(hd):
+    s = _shape(hd, 16)
+    rows = _rows(67, s.r_max)
+    rows["pos"][len(EDGES):] = np.random.default_rng(6).integers(0, 1200, 67 - len(EDGES))
+    calls = [(67, None), (66, None), (65, None), (64, None), (20, None), (19, None), (67, 67), (67, 65), (67, 64),
+             (67, 20), (67, 1), (19, 19), (19, 15), (19, 7), (19, 1), (19, 0), (19, 15)]
+    print(f"[gpu] attention forms 16 x {hd}", flush=True)
+    h0, got = _step_bits(s, rows, calls)
+    h, score, _ = got[0]
+    for (capacity, live), (hc, sc, err) in zip(calls, got):
+        m = capacity if live is None else live
+        assert err == 0
+        assert torch.equal(hc[:m], h[:m]) and torch.equal(sc[:m], score[:m]), (capacity, live)
+        assert torch.equal(hc[m:], h0[m:]), (capacity, live)
+
+
+def test_unmapped_page_in_every_form():
+    """An unmapped page inside a long row's context is reported and left out, alike in the three forms, and reaches no
+    other row."""
+    s = _shape(64, 16)
+    rows = _rows(66, s.r_max)
+    row = EDGES.index(3071)
+    calls = [(66, None), (64, None), (19, None), (19, 15)]
+    print("[gpu] attention forms, an unmapped page", flush=True)
+    _, clean = _step_bits(s, rows, calls[:1])
+    _, got = _step_bits(s, rows, calls, unmap=(row, 100))
+    for (capacity, live), (hc, sc, err) in zip(calls, got):
+        m = capacity if live is None else live
+        assert err == cdb.CDB_DEV_UNMAPPED_PAGE
+        assert torch.equal(hc[:m], got[0][0][:m]) and torch.equal(sc[:m], got[0][1][:m]), (capacity, live)
+    same = (got[0][0] == clean[0][0]).all(1).cpu().numpy()
+    assert not same[row] and same[np.arange(66) != row].all()
