@@ -41,7 +41,7 @@ struct GemmArgs {
 // stripe's 16 rotary pairs for every row, and each row's K/V write page and
 // slot within it.
 struct QkvStage {
-    const float2* rope;  // [rows][16]; NULL: read the call's tables in global memory
+    const float2* rope;  // [rows][16]
     const int* pid;      // [rows]
     const int* tok;      // [rows]
 };
@@ -50,48 +50,11 @@ struct QkvStage {
 __device__ __forceinline__ float rope_first(float xf, float xs, float c, float s) { return fmaf(xf, c, -(xs * s)); }
 __device__ __forceinline__ float rope_second(float xf, float xs, float c, float s) { return fmaf(xs, c, xf * s); }
 
-// split: the workgroup's K split (EPI_PARTIAL writes partial tile `split`)
-template <int EPI>
-__device__ __forceinline__ void epilogue_elem(float val, float partner, int m, int p, int split, const GemmArgs& ga,
-                                              const EpiArgs& ea, const QkvStage& qs) {
-    if (EPI == EPI_STORE) {
-        ea.out[(size_t)m * ea.ld_out + p] = val;
-    } else if (EPI == EPI_PARTIAL) {
-        ga.part[((size_t)split * ga.M + m) * ga.N + p] = val;
-    } else if (EPI == EPI_SWIGLU) {
-        if (p & 16) return;
-        const int f = (p >> 5) * 16 + (p & 15);
-        const float s = val / (1.0f + __expf(-val));
-        ea.act[frag_index(m, f, ea.ld_act)] = f2bf(s * partner);
-    } else {  // EPI_QKV
-        const int g = p >> 5, w = p & 31, half = w >> 4, jj = w & 15;
-        const int gph = ea.hd >> 5;  // groups per head
-        const int hg = ea.H * gph;
-        const int part = g / hg, rem = g - part * hg;
-        const int head = rem / gph, gi = rem - head * gph;
-        const int dim = gi * 16 + jj + half * (ea.hd >> 1);
-        float outv = val;
-        if (part < 2) {
-            const float2 cs = qs.rope ? qs.rope[m * 16 + jj] : ea.rope[(size_t)m * (ea.hd >> 1) + gi * 16 + jj];
-            const float xf = half ? partner : val, xs = half ? val : partner;
-            outv = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
-        }
-        if (part == 0) {
-            ea.q[(size_t)m * (ea.H * ea.hd) + head * ea.hd + dim] = outv;
-            return;
-        }
-        const int pid = qs.rope ? qs.pid[m] : ea.kvpid[m];  // -1: unmapped (reported by the row-entry kernel)
-        if (pid < 0) return;
-        const KvTarget& kv = ea.kv;
-        const int tok = qs.rope ? qs.tok[m] : ea.pos[m] % kPage;
-        kv.pool[kv_offset(kv.layer, pid, kv.n_pages, part - 1, head, ea.H, tok, ea.hd) + dim] = f2bf(outv);
-    }
-}
-
 // Epilogue of the skinny kernel from the reduced tiles fin[ns][n][m] (row
 // pitch fld), with 16-byte stores: each thread takes a run of consecutive
 // output columns of one row (4 fp32 values, or 8 bf16 values in the
-// fragment or K/V layouts).  Same arithmetic per element as epilogue_elem.
+// fragment or K/V layouts).  Same arithmetic per element as tile_epilogue.
+// split: the workgroup's K split (EPI_PARTIAL writes partial tile `split`).
 template <int EPI>
 __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int nt, int NS, int mcap, int split, int tid,
                                                 int nthr, const GemmArgs& ga, const EpiArgs& ea, const QkvStage& qs) {
@@ -136,15 +99,10 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
             *reinterpret_cast<u32x4*>(ea.act + frag_index(m, feat, ea.ld_act)) = u32x4{w[0], w[1], w[2], w[3]};
         }
     } else {  // EPI_QKV: a stripe holds 16 rotary pairs (dims gi*16 + jj and + hd/2) of one head
-      const int mrows = fld - 1;  // rows of a stripe's staged RoPE table
-      for (int ns = 0; ns < NS; ++ns) {
-        const int g = nt + ns, gph = ea.hd >> 5, hg = ea.H * gph;
-        if (g >= (ga.N >> 5)) break;
-        const int part = g / hg, rem = g - part * hg;
+        const int gph = ea.hd >> 5, hg = ea.H * gph;
+        const int part = nt / hg, rem = nt - part * hg;
         const int head = rem / gph, gi = rem - head * gph;
         const int half_hd = ea.hd >> 1;
-        const float* fs = fin + ns * 32 * fld;
-        const float2* srope = qs.rope ? qs.rope + (size_t)ns * mrows * 16 : nullptr;
         if (part == 0) {
             // (m, half, 4-pair run) -> 4 consecutive fp32 q values
             for (int e = tid; e < mcap * 8; e += nthr) {
@@ -153,8 +111,8 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int jj = j4 + i;
-                    const float val = fs[(half * 16 + jj) * fld + m], partner = fs[((half ^ 1) * 16 + jj) * fld + m];
-                    const float2 cs = srope ? srope[m * 16 + jj] : ea.rope[(size_t)m * half_hd + gi * 16 + jj];
+                    const float val = fin[(half * 16 + jj) * fld + m], partner = fin[((half ^ 1) * 16 + jj) * fld + m];
+                    const float2 cs = qs.rope[m * 16 + jj];
                     const float xf = half ? partner : val, xs = half ? val : partner;
                     o[i] = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
                 }
@@ -165,9 +123,9 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
             // (m, half, 8-pair run) -> 8 consecutive bf16 K or V values
             for (int e = tid; e < mcap * 4; e += nthr) {
                 const int m = e >> 2, half = (e >> 1) & 1, j8 = (e & 1) * 8;
-                const int pid = qs.rope ? qs.pid[m] : ea.kvpid[m];  // -1: unmapped (reported by the row-entry kernel)
+                const int pid = qs.pid[m];  // -1: unmapped (reported by the row-entry kernel)
                 if (pid < 0) continue;
-                const int tok = qs.rope ? qs.tok[m] : ea.pos[m] % kPage;
+                const int tok = qs.tok[m];
                 uint32_t w[4];
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
@@ -175,12 +133,11 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
                         const int jj = j8 + i + b;
-                        const float val = fs[(half * 16 + jj) * fld + m];
+                        const float val = fin[(half * 16 + jj) * fld + m];
                         float outv = val;
                         if (part == 1) {
-                            const float partner = fs[((half ^ 1) * 16 + jj) * fld + m];
-                            const float2 cs =
-                                srope ? srope[m * 16 + jj] : ea.rope[(size_t)m * half_hd + gi * 16 + jj];
+                            const float partner = fin[((half ^ 1) * 16 + jj) * fld + m];
+                            const float2 cs = qs.rope[m * 16 + jj];
                             const float xf = half ? partner : val, xs = half ? val : partner;
                             outv = half ? rope_second(xf, xs, cs.x, cs.y) : rope_first(xf, xs, cs.x, cs.y);
                         }
@@ -194,7 +151,6 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
                 *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
             }
         }
-      }
     }
 }
 
@@ -220,7 +176,7 @@ __host__ __device__ constexpr int decode_depth(int MT, int NS) {
 // of them when 8 waves' copies, the reduced block and the q/k/v staging fit in
 // 160 KB of LDS, else one
 __host__ __device__ constexpr int decode_red_tiles(bool qkv, int MT, int NS) {
-    return (8 * NS * MT * 1024 + NS * 32 * (MT * 32 + 1) + (qkv ? NS * MT * 32 * 32 + MT * 64 : 0)) * 4 <= 160 * 1024
+    return (8 * NS * MT * 1024 + NS * 32 * (MT * 32 + 1) + (qkv ? MT * 32 * 32 + MT * 64 : 0)) * 4 <= 160 * 1024
                ? NS * MT : 1;
 }
 
@@ -296,13 +252,13 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     constexpr int RP = MT <= 2 ? MT * 2 : 1;  // MT <= 2: >= mcap * 16 / nthr, as nthr >= 256
     float2 pf_rope[RP];
     int pf_pid = -1, pf_tok = 0;
-    int q_part = 0, q_gi = 0, q_part_last = 0;
+    int q_part = 0, q_gi = 0;
     if constexpr (EPI == EPI_QKV) {
+        static_assert(NS == 1, "the q/k/v epilogue takes one stripe");
         const int gph = ea.hd >> 5, hg = ea.H * gph;
         q_part = nt / hg;
         q_gi = (nt - q_part * hg) % gph;
-        q_part_last = min(nt + NS - 1, stripes - 1) / hg;
-        if (MT <= 2 && NS == 1 && q_part < 2) {
+        if (MT <= 2 && q_part < 2) {
 #pragma unroll
             for (int r = 0; r < RP; ++r) {
                 const int idx = tid + r * nthr;
@@ -310,7 +266,7 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
                     pf_rope[r] = ea.rope[(size_t)(idx >> 4) * (ea.hd >> 1) + q_gi * 16 + (idx & 15)];
             }
         }
-        if (q_part_last > 0 && tid < mcap) {  // a K or V stripe
+        if (q_part > 0 && tid < mcap) {  // a K or V stripe
             pf_pid = ea.kvpid[tid];
             pf_tok = ea.pos[tid] % kPage;
         }
@@ -349,26 +305,20 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     const int fld = MT * 32 + 1;
     QkvStage qs{};
     if constexpr (EPI == EPI_QKV) {
-        // per stripe a [MT*32][16] RoPE table; 32 * fld is even
-        float2* s_rope = reinterpret_cast<float2*>(fin + NS * 32 * fld);
-        int* s_pid = reinterpret_cast<int*>(s_rope + NS * MT * 32 * 16);
+        // a [MT*32][16] RoPE table; 32 * fld is even
+        float2* s_rope = reinterpret_cast<float2*>(fin + 32 * fld);
+        int* s_pid = reinterpret_cast<int*>(s_rope + MT * 32 * 16);
         int* s_tok = s_pid + MT * 32;
-        if (MT <= 2 && NS == 1) {
-            if (q_part < 2) {
+        if (q_part < 2) {  // V: no rotation
+            if constexpr (MT <= 2) {
 #pragma unroll
                 for (int r = 0; r < RP; ++r) {
                     const int idx = tid + r * nthr;
                     if (idx < mcap * 16) s_rope[idx] = pf_rope[r];
                 }
-            }
-        } else {
-            const int gph = ea.hd >> 5, hg = ea.H * gph;
-            for (int ns = 0; ns < NS; ++ns) {
-                const int g = min(nt + ns, stripes - 1);
-                if (g / hg >= 2) continue;  // V: no rotation
-                const int gi = (g % hg) % gph;
+            } else {
                 for (int idx = tid; idx < mcap * 16; idx += nthr)
-                    s_rope[ns * MT * 32 * 16 + idx] = ea.rope[(size_t)(idx >> 4) * (ea.hd >> 1) + gi * 16 + (idx & 15)];
+                    s_rope[idx] = ea.rope[(size_t)(idx >> 4) * (ea.hd >> 1) + q_gi * 16 + (idx & 15)];
             }
         }
         if (tid < mcap) {
@@ -885,7 +835,7 @@ static hipError_t launch_mt(const GemmArgs& ga, const EpiArgs& ea, hipStream_t s
     }
     const int rt = decode_red_tiles(EPI == EPI_QKV, MT, NS);
     size_t lds = ((size_t)ga.KW * (rt > 1 && ga.KW == 8 ? rt : 1) * 1024 + (size_t)NS * 32 * (MT * 32 + 1)) * 4;
-    if (EPI == EPI_QKV) lds += (size_t)NS * MT * 32 * 16 * 8 + (size_t)MT * 32 * 2 * 4;
+    if (EPI == EPI_QKV) lds += (size_t)MT * 32 * 16 * 8 + (size_t)MT * 32 * 2 * 4;
     dim3 grid((ga.N / 32 + NS - 1) / NS, ga.S);
     k_gemm<EPI, MT, NS><<<grid, ga.KW * 64, lds, st>>>(ga, ea);
     return hipGetLastError();
@@ -900,7 +850,11 @@ static hipError_t launch_ns(const GemmArgs& ga, const EpiArgs& ea, hipStream_t s
 
 template <int EPI>
 static hipError_t launch_epi(const GemmArgs& ga, const EpiArgs& ea, int ns, hipStream_t st) {
-    return ns == 2 ? launch_ns<EPI, 2>(ga, ea, st) : launch_ns<EPI, 1>(ga, ea, st);
+    if (ns == 1) return launch_ns<EPI, 1>(ga, ea, st);
+    if constexpr (EPI == EPI_QKV || EPI == EPI_PARTIAL)
+        return hipErrorInvalidValue;  // gemm_shape pairs stripes of gate/up and LM heads only
+    else
+        return launch_ns<EPI, 2>(ga, ea, st);
 }
 
 template <int EPI, int WM>
@@ -940,7 +894,11 @@ static hipError_t launch_tile_passes(const GemmArgs& ga, const EpiArgs& ea, cons
 
 template <int EPI, int WM, int WN>
 static hipError_t launch_tile_shape(const GemmArgs& ga, const EpiArgs& ea, const TileShape& ts, hipStream_t st) {
-    return ga.KW == 8 ? launch_tile_passes<EPI, WM, WN, 2>(ga, ea, ts, st) : launch_tile_passes<EPI, WM, WN, 1>(ga, ea, ts, st);
+    if (ga.KW != 8) return launch_tile_passes<EPI, WM, WN, 1>(ga, ea, ts, st);
+    if constexpr (WN == 4 || (EPI == EPI_QKV && WM == 4))
+        return hipErrorInvalidValue;  // tile_shape gives two parts no such tile
+    else
+        return launch_tile_passes<EPI, WM, WN, 2>(ga, ea, ts, st);
 }
 
 template <int EPI>
