@@ -54,13 +54,13 @@ bool weight_layout(const cdb_model_desc& d, WeightLayout* w) {
 struct ModelGemms {
     GemmShape qkv, o, gu, down, adapter, adapter_part, lm;
 };
-// Launch shapes of the model's projections for calls of M rows: the skinny
-// weight-streaming kernel up to kMaxRows rows, whose sums do not depend on the
-// row count, as the mixed-depth batches need; the tile kernels above, and for
-// prefill chunks from fewer rows on, where they are faster (Ouro widths, skinny
-// -> tile): O and down from 65 rows (10.1 and 13.1 -> 6.5 and 11 us at 66 rows),
-// q/k/v and gate/up from 129 (25.9 and 43.8 -> 19.4 and 28.0 us at 130 rows; at
-// 100 rows the skinny kernel's 17 and 22 us are ahead).
+// Launch shapes of the model's projections for calls of M rows: up to kMaxRows
+// rows those whose sums do not depend on the row count, as the mixed-depth batches
+// need; tile shapes chosen for the row count above, and for prefill chunks from
+// fewer rows on, where they are faster (Ouro widths, skinny -> tile): O and down
+// from 65 rows (10.1 and 13.1 -> 6.5 and 11 us at 66 rows), q/k/v and gate/up from
+// 129 (25.9 and 43.8 -> 19.4 and 19.6 us at 130 rows; at 100 rows the skinny
+// kernel's 17 and 22 us are ahead).
 constexpr int kTileRows = 129, kTilePartialRows = 65;
 static ModelGemms model_gemms(const cdb_model_desc& d, int M, bool prefill) {
     auto shape = [&](int N, int K, int epi) {

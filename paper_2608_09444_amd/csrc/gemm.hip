@@ -629,8 +629,8 @@ __global__ __launch_bounds__(256) void k_gemm_tile(GemmArgs ga, EpiArgs ea, Tile
     if (wave < WM) tile_epilogue<EPI, WM, WN>(sum, (mt0 + wave) * 32 + (lane & 31), live_rows(ga.dn, ga.M), nt0, s, lane, ga, ea);
 }
 
-// Tile GEMM staged through LDS, for gate/up and full-width LM heads above 256
-// rows: (64 WM)-row x 128-column tiles, 4 waves in 2 x 2, each 32 WM rows x 64
+// Tile GEMM staged through LDS, for gate/up above 256 rows and full-width LM heads
+// of prefill chunks: (64 WM)-row x 128-column tiles, 4 waves in 2 x 2, each 32 WM rows x 64
 // columns.  Their grids take more than one round of k_gemm_tile's workgroups
 // (one per CU), where two smaller ones per CU overlap one's start and epilogue
 // with the other's loop: Ouro-shaped gate/up at 512 rows 36 us against 40,
@@ -732,8 +732,12 @@ __global__ __launch_bounds__(256) void k_gemm_lds(GemmArgs ga, EpiArgs ea, int x
         tile_epilogue<EPI, WM, 2>(acc[b], (mt0 + b) * 32 + (lane & 31), ga.M, nt0, 0, lane, ga, ea);
 }
 
-// Which projections above 256 rows take the LDS-staged kernel (see there).
-static bool lds_tiles(int epi, int N) { return epi == EPI_SWIGLU || (epi == EPI_STORE && N >= 8192); }
+// Which projections of prefill chunks take the LDS-staged kernel: gate/up above 256
+// rows (figures at the kernel; up to there k_gemm_tile is ahead, LDS-staged against
+// it at Ouro widths 27.6 and 19.6 us at 130 rows, 29.9 and 22.4 at 256, at Huginn
+// widths 160 and 123, 181 and 139), and wide LM heads at every row count (130 rows
+// 69 and 69 us, 256 rows 83 and 90).
+static bool lds_tiles(int epi, int N, int M) { return (epi == EPI_SWIGLU && M > 256) || (epi == EPI_STORE && N >= 8192); }
 // m-tiles per wave of that kernel: 1 where the rows span an odd number of
 // 64-row tiles, which 128-row tiles would pad by 64 rows (gate/up at 300 rows:
 // 36.0 -> 30.1 us; at 512 rows 64-row tiles gain nothing).
@@ -924,10 +928,11 @@ hipError_t launch_gemm(int epi, const uint16_t* X, const uint16_t* Wp, int M, Ge
         if (M > kMaxPrefillRows || dn) return hipErrorInvalidValue;
         switch (epi) {
             case EPI_QKV: return launch_tile<EPI_QKV>(ga, ea, st);
-            case EPI_SWIGLU: return launch_lds<EPI_SWIGLU>(ga, ea, st);
+            case EPI_SWIGLU:
+                return lds_tiles(epi, g.N, M) ? launch_lds<EPI_SWIGLU>(ga, ea, st) : launch_tile<EPI_SWIGLU>(ga, ea, st);
             case EPI_PARTIAL: return launch_tile<EPI_PARTIAL>(ga, ea, st);
             default:
-                return lds_tiles(epi, g.N) ? launch_lds<EPI_STORE>(ga, ea, st) : launch_tile<EPI_STORE>(ga, ea, st);
+                return lds_tiles(epi, g.N, M) ? launch_lds<EPI_STORE>(ga, ea, st) : launch_tile<EPI_STORE>(ga, ea, st);
         }
     }
     if (g.NS == kTileFixed) {
