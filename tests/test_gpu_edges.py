@@ -252,7 +252,7 @@ def test_row_results_do_not_depend_on_the_batch_ouro_width():
 
 
 def test_row_results_do_not_depend_on_the_batch_huginn_width():
-    # O and down take two stripes per workgroup at 128 rows and one at 50
+    # the projections run in the tile kernel at 128 rows, in the skinny kernel at 50
     s = cdbgen.shrink(cdbgen.HUGINN, n_core=1)
     w = cdbgen.model_weights(cdbgen.HUGINN)
     P = cdbgen.HUGINN.n_prelude

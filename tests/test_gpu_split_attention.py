@@ -93,6 +93,8 @@ def _step_bits(s, rows_np, calls, unmap=None):
     kv.page_table.copy_(torch.from_numpy(pt))
     state = cdb.State(s, n)
     state.h.normal_(0.0, 1.0, generator=g)
+    if s.injection:
+        state.e.normal_(0.0, 1.0, generator=g)
     h0 = state.h.clone()
     ws = cdb.Workspace(gm.desc, n)
     got = []
