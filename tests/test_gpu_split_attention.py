@@ -77,10 +77,11 @@ def test_one_workgroup_form_against_fp32(hd, H):
         assert bool((err <= want.abs() * 2.0 ** -8 + 1e-4).all()), (p, float(err.max()))
 
 
-def _step_bits(s, rows_np, calls, unmap=None):
+def _step_bits(s, rows_np, calls, unmap=None, captured=False):
     """Loop steps of the first `capacity` rows, `live` of them counted on the device (None: the host's count), one
     after the other on one workspace from the same state and cache: [(states, scores, error code)].  unmap: a (row,
-    page) whose entry in the page table is -1."""
+    page) whose entry in the page table is -1.  captured: calls with a device count are replays of one graph per
+    capacity, captured at its first call (after an eager one, which sets the kernels' attributes)."""
     n = len(rows_np["pos"])
     gm = cdb.DeviceModel(s, cdbgen.model_weights(s))
     pt, max_pages, n_pages = _own_pages(s, rows_np)
@@ -97,14 +98,31 @@ def _step_bits(s, rows_np, calls, unmap=None):
         state.e.normal_(0.0, 1.0, generator=g)
     h0 = state.h.clone()
     ws = cdb.Workspace(gm.desc, n)
-    got = []
+    got, graphs = [], {}
     for capacity, live in calls:
         print(f"[gpu]   {capacity} rows, {live} live", flush=True)
+        replay = captured and live is not None
+        if replay and capacity in graphs:
+            graph, count, rows, out = graphs[capacity]
+            count.fill_(live)
+        else:
+            count = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
+            rows = cdb.Rows(*(rows_np[k][:capacity] for k in ("slot", "seq", "pos", "c", "depth")), d_n_rows=count)
+            out = cdb.StepOut(capacity)
+        if replay and capacity not in graphs:
+            cdb.cdb_loop_step(gm.model, kv.c, state.c, rows.c, out.c, ws.buf)
+            torch.cuda.synchronize()
+            graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+            with torch.cuda.graph(graph, stream=side):
+                cdb.cdb_loop_step(gm.model, kv.c, state.c, rows.c, out.c, ws.buf, stream=side)
+            torch.cuda.synchronize()
+            graphs[capacity] = graph, count, rows, out
         state.h.copy_(h0)
-        count = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
-        rows = cdb.Rows(*(rows_np[k][:capacity] for k in ("slot", "seq", "pos", "c", "depth")), d_n_rows=count)
-        out = cdb.StepOut(capacity)
-        cdb.cdb_loop_step(gm.model, kv.c, state.c, rows.c, out.c, ws.buf)
+        torch.cuda.synchronize()
+        if replay:
+            graph.replay()
+        else:
+            cdb.cdb_loop_step(gm.model, kv.c, state.c, rows.c, out.c, ws.buf)
         torch.cuda.synchronize()
         got.append((state.h.clone(), out.score.clone(), cdb.cdb_read_device_error(ws.buf)))
     return h0, got
@@ -113,15 +131,15 @@ def _step_bits(s, rows_np, calls, unmap=None):
 # 16 heads: a row's segments over several workgroups below 20 rows (4 workgroups at 19 rows, so each takes several
 # segments of the long rows), row pairs up to 64 rows (512 pairs), one workgroup per row above; the device count chooses
 # between the last two
-@pytest.mark.parametrize("hd", [64, 96, 128])
-def test_every_form_and_device_count_gives_the_same_bits(hd):
+@pytest.mark.parametrize("hd,captured", [(64, False), (96, False), (128, False), (128, True)])
+def test_every_form_and_device_count_gives_the_same_bits(hd, captured):
     s = _shape(hd, 16)
     rows = _rows(67, s.r_max)
     rows["pos"][len(EDGES):] = np.random.default_rng(6).integers(0, 1200, 67 - len(EDGES))
     calls = [(67, None), (66, None), (65, None), (64, None), (20, None), (19, None), (67, 67), (67, 65), (67, 64),
              (67, 20), (67, 1), (19, 19), (19, 15), (19, 7), (19, 1), (19, 0), (19, 15)]
-    print(f"[gpu] attention forms 16 x {hd}", flush=True)
-    h0, got = _step_bits(s, rows, calls)
+    print(f"[gpu] attention forms 16 x {hd}, captured {captured}", flush=True)
+    h0, got = _step_bits(s, rows, calls, captured=captured)
     h, score, _ = got[0]
     for (capacity, live), (hc, sc, err) in zip(calls, got):
         m = capacity if live is None else live
