@@ -116,3 +116,37 @@ def test_lm_head_of_four_stripes_keeps_its_bits():
         assert torch.equal(logits[:m], first[0][:m]) and torch.equal(ids[:m], first[1][:m]), (capacity, live)
         if live is not None:
             assert bool((logits[live:] == -7.0).all()) and bool((ids[live:] == -7).all())
+
+
+@pytest.mark.parametrize("vocab", [1024, 8192])
+def test_logits_may_start_at_any_float(vocab):
+    """Prefill and coda into logits that are aligned to 4 bytes only: the bits of a 256-byte aligned array."""
+    s = cdbgen.shrink(cdbgen.TINY, name=f"tiny-v{vocab}", vocab=vocab, n_prelude=0, n_core=1, n_coda=0, r_max=1)
+    gm = cdb.DeviceModel(s, cdbgen.model_weights(s))
+    n = 330
+    pages = cdbgen.pages_for(n)
+    kv = cdb.PagedKV(s, 1, pages, 0, pages, 0, fill="random")
+    kv.page_table.copy_(torch.arange(pages, dtype=torch.int32).expand(1, s.r_max + 2, pages))
+    ws = cdb.Workspace(gm.desc, n)
+    state = cdb.State(s, n)
+    state.h.normal_(0.0, 1.0)
+    tok = torch.as_tensor(cdbgen.prompt_ids(vocab, 1, n, seed=98)[0], dtype=torch.int32, device="cuda")
+    ar = np.arange(n, dtype=np.int32)
+    for call, rows in (("prefill", 20), ("prefill", 129), ("prefill", 200), ("prefill", n), ("coda", 20), ("coda", 140),
+                       ("coda", 256)):
+        print(f"[gpu] {call} of {rows} rows, vocabulary {vocab}, logits at every float of 16 bytes", flush=True)
+        want = None
+        for first in range(4):
+            buf = torch.full((rows * vocab + 8,), -7.0, dtype=torch.float32, device="cuda")
+            logits = buf[first:first + rows * vocab]
+            ids = torch.empty(rows, dtype=torch.int32, device="cuda")
+            if call == "prefill":
+                cdb.cdb_prefill(gm.model, kv.c, 0, 0, tok[:rows], logits, ids, ws.buf)
+            else:
+                r = cdb.Rows(ar[:rows], np.zeros(rows, np.int32), ar[:rows])
+                cdb.cdb_boundary_coda(gm.model, kv.c, state.c, r.c, logits, ids, ws.buf)
+            torch.cuda.synchronize()
+            assert cdb.cdb_read_device_error(ws.buf) == 0
+            want = want or (logits, ids)
+            assert torch.equal(logits, want[0]) and torch.equal(ids, want[1]), (call, rows, first)
+            assert bool((buf[:first] == -7.0).all()) and bool((buf[first + rows * vocab:] == -7.0).all())
