@@ -242,12 +242,17 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
  *   d_error: device int32, required; receives the sticky device error codes
  *   (CDB_DEV_*) that cdb_loop_step keeps in its workspace.  The caller zeroes
  *   it once and reads (and re-zeroes) it outside the hot path.
- * Calls whose workspace without what only speeds them up would exceed
- * 48 MiB (e.g. more than 256 rows of the Ouro-shaped model) return
- * CDB_ERR_CAPACITY before anything is enqueued.  Nothing carries over between
- * calls in the scratch.  Every call on one GPU shares its scratch: calls that
- * overlap on a GPU (different streams without ordering, several threads) race
- * and must not be issued. */
+ * Calls that need more than 48 MiB of it return CDB_ERR_CAPACITY before
+ * anything is enqueued.  What n rows need (the array's other 36 MiB hold what
+ * only speeds calls up, and are not reckoned):
+ *   n (12 d + 4 P d + 4 head_dim + 24) + R (4 d + 2 d_ff) + 128 vocab
+ * bytes, each of its 13 regions (the first of 256) rounded up to 256, with
+ * R = n rounded up to 32, 64, 128 or 256, and P the largest, over K = d, d_ff
+ * and (with injection) 2 d, of: 1, doubled while P d < 8192 and K >= 2048 P.
+ * All 256 rows of the Ouro-shaped model fit; of wider models fewer.  Nothing
+ * carries over between calls in the scratch.  Every call on one GPU shares its
+ * scratch: calls that overlap on a GPU (different streams without ordering,
+ * several threads) race and must not be issued. */
 cdb_status cdb_loop_step_noalloc(const cdb_model* model, const cdb_kv* kv, const cdb_state* state,
                                  const cdb_rows* rows, const cdb_step_out* out, int32_t* d_error, hipStream_t stream);
 
@@ -273,7 +278,9 @@ cdb_status cdb_boundary_coda(const cdb_model* model, const cdb_kv* kv, const cdb
  * what each plane's page holds: with aliased planes (the shared layouts) that
  * is an earlier chunk's last loop, so chunking matches one whole-prompt block
  * under the full layout only.  Attention is query-tiled on
- * MFMA; above 256 rows the projections use compute-bound tiles.
+ * MFMA; from 65 rows (O and down) and 129 rows (the others) the projections run
+ * as tiles whose split of a sum may follow the row count, so chunking a prompt
+ * differently changes roundings.
  * 1 <= n_rows <= 512, else CDB_ERR_CAPACITY (an empty chunk has no last row to
  * take an id from); the workspace must be sized for n_rows.  One call spans at
  * most 10240 positions: pos0 + n_rows > 10240 returns CDB_ERR_CAPACITY before

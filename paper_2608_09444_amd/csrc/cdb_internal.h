@@ -100,10 +100,10 @@ struct EpiArgs {
 
 struct GemmShape {
     int N, K, S, KW;  // packed output columns, reduction length, K splits over workgroups, waves per workgroup
-    int NS;           // 32-column stripes per workgroup (1 or 2), or kTileShapes: the tile kernels
+    int NS;           // 32-column stripes per workgroup (1 or 2) of the skinny kernel, or which tile kernels:
 };
-constexpr int kTileShapes = 4;
-constexpr int kTileFixed = 5;  // or: the register tile kernel at the given splits
+constexpr int kTileShapes = 4;  // at splits chosen for the row count (prefill chunks)
+constexpr int kTileFixed = 5;   // the register tile kernel at the skinny kernel's splits
 struct TileShape {
     int WM, WN, gx, gy, S;  // m-tiles and stripes per workgroup, column and row groups, K splits
 };
@@ -149,7 +149,9 @@ __host__ __device__ __forceinline__ int attn_segment_pages(int npg) {
 // over several workgroups.  One workgroup per row and head against several, 16
 // heads: 12 rows at 3100 positions 111 and 73 us, at 450 positions 21 and 19; 20
 // rows at 3100 positions (320 pairs) 117 and 116; 30 rows 128 and 168, 24 rows
-// at 450 positions 23 and 28; 9 rows of 55 heads 25 and 28.6.
+// at 450 positions 23 and 28; 9 rows of 55 heads 25 and 28.6.  The host's row count
+// decides (it fixes the grid): a call of a larger capacity whose device count is
+// small keeps one workgroup per row and head.
 constexpr int kAttnSplitItems = 320;
 // Scratch of that form: segment records (attn_part_floats per row) and one
 // arrival counter per (row, head), zero between launches.

@@ -367,7 +367,8 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs ga, EpiArgs ea) {
     stripe_epilogue<EPI>(fin, fld, nt, NS, mcap, s, tid, nthr, ga, ea, qs);
 }
 
-// Tile GEMM of prefill chunks.
+// Register tile GEMM: prefill chunks, and loop steps, preludes and codas of more rows
+// than the skinny kernel takes (gemm_shape).
 //
 // A workgroup owns a (32 WM)-row x (32 WN)-column output tile and one K split;
 // its 4 waves (one per SIMD, up to 512 registers each) split that K range and
@@ -473,7 +474,8 @@ __device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, 
     }
 }
 
-// floats of LDS of the exchange: every wave's stripes of the m-tiles it does not sum
+// Stripes per round of the exchange: all of them where the four waves' copies of WM x
+// WN tiles fit in LDS, else half.
 __host__ __device__ constexpr int tile_exchange_stripes(int WM, int WN) {
     return 4 * WM * WN * 1024 * 4 <= 160 * 1024 ? WN : (WN + 1) / 2;
 }
@@ -748,7 +750,8 @@ static int lds_wave_mtiles(int M) { return ((M + 63) / 64) % 2 ? 1 : 2; }
 // two parts of K each.
 TileShape tile_shape(int N, int K, int M, int epi, int fixed_S, bool two_parts) {
     const int mt = (M + 31) / 32, stripes = N / 32, KS = K / 16;
-    // (the two-part kernel with q/k/v's epilogue spills at 4 m-tiles: 39 us against 24 at 200 Ouro-shaped rows)
+    // (two parts over 4 x 3 tiles spill: 192 registers with q/k/v's epilogue, 39 us against 24 with 3 m-tiles at 200
+    // Ouro-shaped rows; 79 with the others, where the fewer rounds are worth it: gate/up 31 us against 40)
     const int most = two_parts && epi == EPI_QKV ? 3 : 4, gy = (mt + most - 1) / most, WM = std::max(3, (mt + gy - 1) / gy);
     TileShape best{};
     double cost = 1e30;
@@ -795,6 +798,10 @@ GemmShape gemm_shape(int N, int K, int epi, int M) {
     // stripes fill the chip once in the tile kernel (3 ways for 165 stripes); in
     // the skinny kernel two such workgroups share a CU (9 rows, O, down and
     // adapter together: 304 -> 246 us per step against 2 ways and 8 waves).
+    // Where 8 waves fill the chip in one round, 4 cost the skinny kernel up to 2%
+    // of a step and give the tile kernel more: 2 layers of d 3072 at 48 rows 304
+    // and 299 us, at 160 rows 532 and 573; 1 layer of d 8192 at 64 rows 581 and
+    // 572, at 65 rows 538 and 590 (4 waves against 8).
     if (KS / S >= 160) {
         int T = 1;
         if (epi == EPI_PARTIAL) {

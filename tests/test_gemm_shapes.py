@@ -1,10 +1,11 @@
-"""The launch shapes of the projections, on the host: every shape the dispatch
-gives a call has a kernel, for every width the model descriptor accepts.  CPU
-only (the shape functions launch nothing)."""
+"""Host arithmetic of the library: every launch shape of a projection that the dispatch
+gives has a kernel, and the no-allocation step takes the calls that libcdb.h says.  CPU
+only (these functions launch nothing)."""
 import ctypes as C
 
 import pytest
 
+import cdbgen
 import paper_2608_09444_amd as cdb
 
 QKV, PARTIAL, SWIGLU, STORE = range(4)
@@ -66,3 +67,41 @@ def test_every_launch_shape_has_a_kernel(d):
                 assert g.NS == TILE_SHAPES
                 _check_tile(N, K, M, epi, 0, False, (N, K, epi, M))
                 _check_tile(N, K, M, epi, g.S, False, (N, K, epi, M))
+
+
+class WsLayout(C.Structure):
+    _fields_ = [(n, C.c_size_t) for n in ("err", "h", "h_in", "q", "x", "act", "part", "rope", "order", "kvpid", "deff",
+                                          "prow", "lm", "base", "apart", "arrive", "total")]
+
+
+def _need(s, n):
+    """The bytes that decide whether cdb_loop_step_noalloc takes n rows, as libcdb.h states them."""
+    def splits(K):
+        P = 1
+        while P * s.d < 8192 and K >= 2048 * P:
+            P *= 2
+        return P
+    P = max(splits(K) for K in (s.d, s.d_ff) + ((2 * s.d,) if s.injection else ()))
+    R = next(r for r in (32, 64, 128, 256) if n <= r)
+    regions = [256, 4 * n * s.d, 4 * n * s.d, 4 * n * s.d, 4 * R * s.d, 2 * R * s.d_ff, 4 * n * P * s.d, 4 * n * s.head_dim,
+               4 * n, 4 * n, 4 * n, 12 * n, 128 * s.vocab]
+    assert abs(sum(regions) - 256 - (n * (12 * s.d + 4 * P * s.d + 4 * s.head_dim + 24) + R * (4 * s.d + 2 * s.d_ff) +
+                                     128 * s.vocab)) == 0
+    return sum((b + 255) // 256 * 256 for b in regions)
+
+
+def test_no_allocation_limit_is_the_stated_one():
+    layout = _fn("_ZN3cdb9ws_layoutERK14cdb_model_descib", WsLayout, C.c_void_p, C.c_int, C.c_bool)
+    shapes = [cdbgen.TINY, cdbgen.OURO, cdbgen.HUGINN]
+    for d_ff in (96, 5632, 16384, 46816, 68928):
+        for H, hd in ((1, 64), (3, 96), (16, 128), (32, 128), (55, 96), (64, 128), (330, 96)):
+            shapes += [cdbgen.shrink(cdbgen.OURO, d=H * hd, n_heads=H, head_dim=hd, d_ff=d_ff, injection=i) for i in (0, 1)]
+    for s in shapes:
+        desc = cdb.make_desc(s)
+        for n in (1, 2, 19, 32, 33, 64, 65, 100, 128, 129, 223, 256):
+            w = layout(C.addressof(desc), n, False)
+            assert w.base == _need(s, n), (s, n)
+            if w.base <= 48 << 20:
+                assert w.total <= 84 << 20, (s, n)  # the static array holds every call that is accepted
+    ouro = cdb.make_desc(cdbgen.OURO)
+    assert layout(C.addressof(ouro), cdb.MAX_ROWS, False).base <= 48 << 20
