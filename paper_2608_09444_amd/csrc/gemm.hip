@@ -50,11 +50,16 @@ struct QkvStage {
 __device__ __forceinline__ float rope_first(float xf, float xs, float c, float s) { return fmaf(xf, c, -(xs * s)); }
 __device__ __forceinline__ float rope_second(float xf, float xs, float c, float s) { return fmaf(xs, c, xf * s); }
 
-// Four floats of a plain store: the caller's logits may start at any float, and
-// 16-byte stores need no more than that alignment on this part.
+// Four floats of a split partial (a 16-byte aligned workspace region) or of a plain
+// store: the caller's logits may start at any float, and 16-byte stores need no
+// more than that alignment on this part.
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void store4_any(float* dst, float a, float b, float c, float d) {
-    *reinterpret_cast<floatx4_any*>(dst) = floatx4_any{a, b, c, d};
+template <int EPI>
+__device__ __forceinline__ void store4(float* dst, float a, float b, float c, float d) {
+    if (EPI == EPI_PARTIAL)
+        *reinterpret_cast<float4*>(dst) = make_float4(a, b, c, d);
+    else
+        *reinterpret_cast<floatx4_any*>(dst) = floatx4_any{a, b, c, d};
 }
 
 // Epilogue of the skinny kernel from the reduced tiles fin[ns][n][m] (row
@@ -75,7 +80,7 @@ __device__ __forceinline__ void stripe_epilogue(const float* fin, int fld, int n
             if (nt + ns >= (ga.N >> 5)) break;
             const int m = r >> 3, c4 = (r & 7) * 4;
             const float* f = fin + ns * 32 * fld + c4 * fld + m;
-            store4_any(base + (size_t)m * ld + (nt + ns) * 32 + c4, f[0], f[fld], f[2 * fld], f[3 * fld]);
+            store4<EPI>(base + (size_t)m * ld + (nt + ns) * 32 + c4, f[0], f[fld], f[2 * fld], f[3 * fld]);
         }
     } else if (EPI == EPI_SWIGLU) {
         // (ns, m, 8-feature run): gate columns c8 .. c8 + 7, up columns 16 + c8 ..
@@ -469,7 +474,7 @@ __device__ __forceinline__ void tile_epilogue(const floatx16 (&acc)[WN], int m, 
                          (nt0 + a) * 32 + half * 4;
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                store4_any(dst + u * 8, acc[a][u * 4], acc[a][u * 4 + 1], acc[a][u * 4 + 2], acc[a][u * 4 + 3]);
+                store4<EPI>(dst + u * 8, acc[a][u * 4], acc[a][u * 4 + 1], acc[a][u * 4 + 2], acc[a][u * 4 + 3]);
         }
     }
 }
