@@ -236,7 +236,7 @@ cdb_status cdb_loop_step_gated(const cdb_model* model, const cdb_kv* kv, const c
 
 /* cdb_loop_step for callers that cannot allocate memory (code under HIP graph
  * capture, serving loops and harnesses that forbid allocation): the same
- * computation and outputs, with its scratch taken from a 84 MiB array the
+ * computation and outputs, with its scratch taken from an 84 MiB array the
  * library keeps in device memory (one per GPU, held until the process ends)
  * instead of a workspace argument.  It allocates and frees nothing.
  *   d_error: device int32, required; receives the sticky device error codes
